@@ -546,6 +546,23 @@ static nn_status make_desc_const(const nn_mbp_params* p, DescConst* out) {
   P.rc64 = p->rc;
   P.half_pi_over_rc64 = 0.5 * M_PI / p->rc;
   P.pi_over_rc64 = M_PI / p->rc;
+  if (!bp) {
+    const double sa = sqrt(p->eta_ang * M_LOG2E), sr = sqrt(p->eta_rad * M_LOG2E);
+    P.eps_tile = (float)std::max(p->eps, 1e-30);
+    P.ra_scale = 0.5 * sa;
+    P.rr_scale = sr;
+    P.key_scale = (float)(1048000.0 / p->rc);
+    P.dravg = (float)-sqrt(p->eta_ang * M_LN2);
+    P.drr = (float)(-2.0 * sqrt(p->eta_rad * M_LN2));
+    for (int k = 0; k < p->n_rad; ++k) {
+      P.rs_rad_sc[k] = (float)(sr * p->rs_rad[k]);
+      P.rs_rad_sc_lo[k] = (float)(sr * p->rs_rad[k] - (double)P.rs_rad_sc[k]);
+    }
+    for (int q = 0; q < p->n_rs_ang; ++q) {
+      P.rs_ang_sc[q] = (float)(sa * p->rs_ang[q]);
+      P.rs_ang_sc_lo[q] = (float)(sa * p->rs_ang[q] - (double)P.rs_ang_sc[q]);
+    }
+  }
   *out = P;
   return NN_OK;
 }

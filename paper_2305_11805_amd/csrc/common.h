@@ -54,6 +54,14 @@ struct DescConst {
   float rs_rad[kMaxRad], rs_rad_lo[kMaxRad];   // centre = hi + lo (double-float)
   float rs_ang[kMaxRsAng], rs_ang_lo[kMaxRsAng];
   double rc64, half_pi_over_rc64, pi_over_rc64;
+  // the tile passes' scaled distances: ra = sqrt(eta_ang log2 e) r / 2, so
+  // that the angular Gaussian is 2^(-(ra_j + ra_k - rs_ang_sc)^2), and rr =
+  // sqrt(eta_rad log2 e) r for the radial one; the centres scaled alike
+  // (hi + lo); key_scale: r < rc to an integer below 2^20
+  double ra_scale, rr_scale;
+  float eps_tile;  // eps_ang, at least 1e-30 (their square roots take no zero)
+  float key_scale, dravg, drr;  // d ln R / d rbar / 2 and d ln g / dr per unit of the scaled difference
+  float rs_rad_sc[kMaxRad], rs_rad_sc_lo[kMaxRad], rs_ang_sc[kMaxRsAng], rs_ang_sc_lo[kMaxRsAng];
   // standard BP angular term (kind 1): per angle term p the prefactor
   // 2 * 2^(1 - zeta_p) (both orders of each neighbor pair), lambda_p and the
   // integer exponent; per radius term q its width eta_q

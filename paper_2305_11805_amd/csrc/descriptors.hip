@@ -1,40 +1,34 @@
-// mBP descriptors and their adjoint on gfx950.
+// Descriptor passes on gfx950: the packed passes for short rows (four atoms
+// per wave), the standard BP term's forward and adjoint, the descriptor
+// tangent, the stored Jacobian and its contraction, and the force gather.
+// The mBP term's passes over longer rows are in desc_tiles.hip.
 //
-// One 64-lane wave per atom.  The wave stages the atom's neighbors inside rc
-// in LDS, sorted by species (stable).  Per neighbor the pair geometry is
-// formed once from FP64 positions -- d = (x_j - x_i) + image shift, r, the
-// unit vector d/r, rc - r and the cosine cutoff -- and rounded to FP32 only
-// after the subtractions that would otherwise cancel (r is kept as a hi/lo
-// float pair).  Everything per triplet is FP32.
+// The one-atom passes stage the atom's neighbors inside rc in LDS, sorted by
+// species (stable).  Per neighbor the pair geometry is formed once from FP64
+// positions -- d = (x_j - x_i) + image shift, r, the unit vector d/r, rc - r
+// and the cosine cutoff -- and rounded to FP32 only after the subtractions
+// that would otherwise cancel (r is kept as a hi/lo float pair).  Everything
+// per triplet is FP32.
 //
-// Forward (radial + angular descriptor, Sec. II.A / III.A):
-//   radial: lane k owns radial bin k and sums over the neighbors of each
-//   species segment;
-//   angular: for every unordered species pair block (a <= b) the block's
-//   triplets are taken 64 at a time; the bins are the sum over triplets of
-//   the separable outer product  A_p(theta) * R_q(r_avg) * 2 fc fc, which
-//   runs on the 4x4x1 FP32 MFMA (each lane forms one triplet's geometry, then
-//   four lanes share a triplet and supply its angle and radius factors).
+// Descriptor (Sec. II.A / III.A): lane k owns radial bin k; for every
+// unordered species pair block the block's triplets are taken 64 at a time,
+// and the bins, a sum over triplets of the separable outer product
+// A_p(theta) * R_q, run on the 4x4x1 FP32 MFMA.
 //
 // Adjoint (forces, Sec. II: forces are derivatives of the energy): given
-// lambda_i = dE_i/dG_i, produce dE_i/dd_e for every neighbor entry e.
-//   radial: lane <-> neighbor;
-//   angular: lane <-> neighbor j on a circular schedule: at step s lane j
-//   takes the pair (j, (j + s) mod n), so every unordered pair is visited
-//   once and, within one step, no two lanes touch the same partner k.  The
-//   j-side gradient accumulates in registers, the k-side one is added to a
-//   per-neighbor LDS slot; since no two lanes of an instruction share a slot
-//   and instructions retire in program order, the sums are bitwise
-//   reproducible.
+// lambda_i = dE_i/dG_i, produce dE_i/dd_e for every neighbor entry e.  Lane
+// <-> neighbor j on a circular schedule: at step s lane j takes the pair (j,
+// (j + s) mod n), so every unordered pair is visited once and, within one
+// step, no two lanes touch the same partner k: plain LDS adds, in a fixed
+// order.
 #include <math.h>
 
 #include <type_traits>
 
 #include "common.h"
+#include "desc_ops.h"
 
 namespace nnp {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 struct AtomNb {
   float4 d[kMaxNb];   // unit vector d/r (x, y, z), r (hi)
@@ -45,84 +39,13 @@ struct AtomNb {
   int bad;
 };
 
-__device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
-// Orders this wave's LDS accesses: writes before it are seen by reads after
-// it in every lane, and the compiler moves no LDS access across it.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-// Keeps this wave's LDS accesses in program order without waiting for them
-// to complete: the LDS serves one wave's instructions in the order they are
-// issued, so a read issued after a write of the same address by any lane of
-// the wave returns the written value.  Only the compiler has to be kept from
-// moving or caching accesses across it.
-__device__ __forceinline__ void wave_lds_order() { __asm__ volatile("" ::: "memory"); }
-__device__ __forceinline__ int nb_species(const float4& f) { return __float_as_int(f.w) & 15; }
-__device__ __forceinline__ int nb_entry(const float4& f) { return __float_as_int(f.w) >> 4; }
-
-// The structure of atom i: the largest c < B with atom_ptr[c] <= i.  Each
-// round the 64 lanes probe 64 evenly spaced positions of the remaining range
-// and one ballot keeps the stretch after the last probe at or below i, so
-// 2048 structures take two dependent rounds of loads instead of eleven.
-// Every lane of the wave must call it (with the same i).
-__device__ __forceinline__ int struct_of_atom(const int64_t* atom_ptr, int32_t B, int64_t i) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, hi = B;  // atom_ptr[lo] <= i; the answer lies in [lo, hi)
-  while (hi - lo > 1) {
-    const int step = (hi - lo + 63) / 64;
-    const int p = lo + lane * step;
-    const uint64_t le = __ballot(p < hi && atom_ptr[p] <= i);  // a prefix of the lanes: atom_ptr does not decrease
-    lo += (__popcll(le) - 1) * step;
-    hi = min(hi, lo + step);
-  }
-  return lo;
-}
-
-// The atom a one-atom-per-block descriptor launch works on.  With the
-// list's bin order (kept by the list build) the grid is whole rounds of the
-// eight XCDs and block b takes slot (b mod 8) * per + b / 8 of that order:
-// consecutive blocks go to different XCDs, so each XCD walks one contiguous
-// stretch of space and the neighbor positions its atoms gather stay in its
-// L2.  Without the order, or while the list is not valid (the order is then
-// not a permutation), the slot is the atom.  -1 for slots past the atoms.
-__device__ __forceinline__ int64_t atom_of_block(const int32_t* __restrict__ order, int64_t N, bool valid) {
-  int64_t slot = blockIdx.x;
-  if (order) slot = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-  if (slot >= N) return -1;
-  return (order && valid) ? (int64_t)order[slot] : slot;
-}
-
-// Blocks of such a launch: whole rounds of the eight XCDs with the order.
-static inline unsigned atom_grid(int64_t N, const int32_t* order) {
-  return (unsigned)(order ? (N + 7) / 8 * 8 : N);
-}
-
 constexpr int kStageRounds = 2;  // rows up to 128 entries are staged in one pass
 
-// Packed passes: kPackAtoms atoms per wave, kPackLanes lanes per atom in the
-// per-atom phases.  An atom is packed when its row has at most kPackNb
-// entries; longer rows go to the one-atom kernels.
-constexpr int kPackAtoms = 4;
-constexpr int kPackLanes = 16;
-constexpr int kPackNb = 32;
 // LDS stride of a group's neighbor slots: one spare slot per group puts the
 // same slot of the four groups on different LDS banks (at 32 the four
 // regions start on one bank, and lanes of different atoms at the same
 // offset conflict)
 constexpr int kPackSlots = kPackNb + 1;
-
-// sin and cos of x in [0, pi/2] by their Taylor series to x^11 and x^12
-// (truncation below 6e-8 at pi/2), without range reduction.
-__device__ __forceinline__ void sincos_quarter(float x, float& sn, float& cs) {
-  const float z = x * x;
-  sn = x * fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, -2.5052108e-8f, 2.7557319e-6f), -1.9841270e-4f), 8.3333333e-3f),
-                        -1.6666667e-1f), 1.0f);
-  cs = fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, 2.0876757e-9f, -2.7557319e-7f), 2.4801587e-5f), -1.3888889e-3f),
-                        4.1666667e-2f), -0.5f), 1.0f);
-}
 
 // The staged record of one neighbor inside rc from its FP64 displacement d
 // (|d|^2 = r2): (d/r, r hi), (fc, dfc/dr, r lo, entry << 4 | species), 1/r.
@@ -337,77 +260,6 @@ __device__ void stage_neighbors(AtomNb& nb, int64_t i, const nn_system& sys, con
   __syncthreads();
 }
 
-// x^e for a small positive integer e, on an array (exponent bits outside).
-template <int N>
-__device__ __forceinline__ void ipow_array(const float (&x)[N], int e, float (&out)[N]) {
-  float base[N];
-#pragma unroll
-  for (int p = 0; p < N; ++p) {
-    out[p] = 1.0f;
-    base[p] = x[p];
-  }
-  while (e) {
-    if (e & 1) {
-#pragma unroll
-      for (int p = 0; p < N; ++p) out[p] *= base[p];
-    }
-    e >>= 1;
-    if (e) {
-#pragma unroll
-      for (int p = 0; p < N; ++p) base[p] *= base[p];
-    }
-  }
-}
-
-// x^E for a compile-time E (fully unrolled); E = 0 selects the runtime loop.
-template <int E, int N>
-__device__ __forceinline__ void ipow_sel(const float (&x)[N], int e_runtime, float (&out)[N]) {
-  if constexpr (E == 0) {
-    ipow_array<N>(x, e_runtime, out);
-  } else {
-    float base[N];
-    bool first = true;
-#pragma unroll
-    for (int p = 0; p < N; ++p) base[p] = x[p];
-#pragma unroll
-    for (int bit = 0; bit < 11; ++bit) {
-      if ((E >> bit) == 0) break;
-      if ((E >> bit) & 1) {
-#pragma unroll
-        for (int p = 0; p < N; ++p) out[p] = first ? base[p] : out[p] * base[p];
-        first = false;
-      }
-      if ((E >> (bit + 1)) != 0) {
-#pragma unroll
-        for (int p = 0; p < N; ++p) base[p] *= base[p];
-      }
-    }
-  }
-}
-
-// q = t / n, r = t mod n for 0 <= t < 2^24 and 0 < n < 2^12, through a
-// float reciprocal: the float quotient is off by at most one.
-__device__ __forceinline__ void divmod_small(int t, int n, float inv_n, int& q, int& r) {
-  q = (int)((float)t * inv_n);
-  r = t - q * n;
-  if (r < 0) {
-    --q;
-    r += n;
-  } else if (r >= n) {
-    ++q;
-    r -= n;
-  }
-}
-
-__device__ __forceinline__ int pair_block(int S, int a, int b) {
-  if (a > b) {
-    int t = a;
-    a = b;
-    b = t;
-  }
-  return a * S - a * (a - 1) / 2 + (b - a);
-}
-
 // Angle terms of one triplet from the two unit vectors: cos(theta), the
 // smoothed sine sqrt(sin^2 + eps), and the average radius as hi (exact half
 // of a rounded sum) + lo (the rounding error of that sum plus the lo parts).
@@ -519,8 +371,8 @@ __device__ __forceinline__ BpSide bp_side64(const double* __restrict__ dj, const
 
 constexpr int kFuseTriplets = 256;  // triplets per atom for the pair-block-per-MFMA-block forward
 
-// The descriptor row of atom i by the block (WPA waves).
-template <int NT, int NRA, int WPA, int ZC>
+// The BP descriptor row of atom i by the block (WPA waves).
+template <int NT, int NRA, int WPA>
 __device__ __forceinline__ void desc_fwd_atom(int64_t i, bool list_ok, const nn_system& sys,
                                               const int64_t* __restrict__ offsets, const int32_t* __restrict__ nbr,
                                               const int8_t* __restrict__ shift, const DescConst& P,
@@ -529,23 +381,22 @@ __device__ __forceinline__ void desc_fwd_atom(int64_t i, bool list_ok, const nn_
   __shared__ AtomNb nb;
   // per-wave partial sums (radial bins: S * n_rad <= 512; angular block: NB)
   __shared__ float xch[WPA > 1 ? WPA * NN_MAX_SPECIES * kMaxRad : 1];
-  __shared__ float4 tgeo[WPA][kWave];  // per chunk: cos, smoothed sine, average radius (hi, lo)
-  __shared__ float tf2[WPA][kWave];    // and 2 fc fc
-  __shared__ double d64[ZC == kZcBP ? 3 * kMaxNb : 1];  // BP: FP64 displacements for the third side
+  __shared__ float4 tgeo[WPA][kWave];  // per chunk: 1 + cos, 1 - cos, the sum of the squared sides
+  __shared__ float tf2[WPA][kWave];    // and the three cutoffs
+  __shared__ double d64[3 * kMaxNb];   // FP64 displacements for the third side
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   float* Gi = G + i * (int64_t)P.D;
   if (!list_ok) {  // no valid list: never read its entries
     for (int d = tid; d < P.D; d += 64 * WPA) Gi[d] = 0.f;
     return;
   }
-  stage_neighbors(nb, i, sys, offsets, nbr, shift, P, meta, nullptr, ZC == kZcBP ? d64 : nullptr);
+  stage_neighbors(nb, i, sys, offsets, nbr, shift, P, meta, nullptr, d64);
   if (nb.bad) {
     for (int d = tid; d < P.D; d += 64 * WPA) Gi[d] = 0.f;
     return;
   }
   const int S = P.S;
   const float eta_r2 = P.eta_rad * 1.4426950408889634f;
-  const float eta_a2 = P.eta_ang * 1.4426950408889634f;
   // radial bins: lane k owns bin k; wave w sums the neighbors t = w mod WPA
   for (int k0 = 0; k0 < P.n_rad; k0 += kWave) {
     const int k = k0 + lane;
@@ -579,73 +430,40 @@ __device__ __forceinline__ void desc_fwd_atom(int64_t i, bool list_ok, const nn_
   constexpr int NP = NT / 4, NQ = NRA / 4;
   const int li = lane & 3, blk = lane >> 2;
   // this lane's angle terms p = 4u + li and radius terms q = 4v + li
-  float xa[NP], xb[NP], rsq[NQ], rsq_lo[NQ];
+  float xa[NP], xb[NP], rsq[NQ];
   int zexp[NP];
 #pragma unroll
   for (int u = 0; u < NP; ++u) {
-    if constexpr (ZC == kZcBP) {
-      xa[u] = P.bp_pref[4 * u + li];
-      xb[u] = P.bp_lam[4 * u + li];
-      zexp[u] = P.bp_zeta[4 * u + li];
-    } else {
-      xa[u] = P.x_a[4 * u + li];
-      xb[u] = P.x_b[4 * u + li];
-      zexp[u] = 0;
-    }
+    xa[u] = P.bp_pref[4 * u + li];
+    xb[u] = P.bp_lam[4 * u + li];
+    zexp[u] = P.bp_zeta[4 * u + li];
   }
 #pragma unroll
-  for (int u = 0; u < NQ; ++u) {
-    if constexpr (ZC == kZcBP) {
-      rsq[u] = P.bp_eta[4 * u + li] * 1.4426950408889634f;
-      rsq_lo[u] = 0.f;
-    } else {
-      rsq[u] = P.rs_ang[4 * u + li];
-      rsq_lo[u] = P.rs_ang_lo[4 * u + li];
-    }
-  }
-  // one triplet's geometry: (cos, smoothed sine, average radius hi, lo)
-  // and 2 fc fc for mBP; (1 + cos, 1 - cos, sum of the squared sides) and
-  // the three cutoffs for BP
+  for (int u = 0; u < NQ; ++u) rsq[u] = P.bp_eta[4 * u + li] * 1.4426950408889634f;
+  // one triplet's geometry: 1 + cos, 1 - cos, the sum of the squared sides,
+  // and the three cutoffs
   auto trip_geom = [&](int j, int k, float4& geo, float& F2) {
     const float4 fu = nb.f[j], fv = nb.f[k];
-    if constexpr (ZC == kZcBP) {
-      // 1 + cos and 1 - cos as |u^ +- v^|^2 / 2 (no cancellation near
-      // cos = -+1); the third side from the FP64 displacements, with
-      // rc - r_jk = (rc^2 - r_jk^2) / (rc + r_jk), so that its cutoff
-      // keeps its relative precision up to rc
-      const float4 u = nb.d[j], v = nb.d[k];
-      const float px = u.x + v.x, py = u.y + v.y, pz = u.z + v.z;
-      const float mx = u.x - v.x, my = u.y - v.y, mz = u.z - v.z;
-      const BpSide w3 = bp_side64(d64 + 3 * j, d64 + 3 * k, P);
-      geo = make_float4(0.5f * fmaf(px, px, fmaf(py, py, pz * pz)), 0.5f * fmaf(mx, mx, fmaf(my, my, mz * mz)),
-                        fmaf(u.w, u.w, fmaf(v.w, v.w, w3.rw2)), 0.f);
-      F2 = fu.x * fv.x * w3.fw;  // three cutoffs
-    } else {
-      const TripGeom g = triplet_geom(nb.d[j], fu, nb.d[k], fv, P.eps_ang);
-      geo = make_float4(g.c, g.ssm, g.rbar, g.rbar_lo);
-      F2 = 2.0f * fu.x * fv.x;
-    }
+    // 1 + cos and 1 - cos as |u^ +- v^|^2 / 2 (no cancellation near
+    // cos = -+1); the third side from the FP64 displacements, with
+    // rc - r_jk = (rc^2 - r_jk^2) / (rc + r_jk), so that its cutoff
+    // keeps its relative precision up to rc
+    const float4 u = nb.d[j], v = nb.d[k];
+    const float px = u.x + v.x, py = u.y + v.y, pz = u.z + v.z;
+    const float mx = u.x - v.x, my = u.y - v.y, mz = u.z - v.z;
+    const BpSide w3 = bp_side64(d64 + 3 * j, d64 + 3 * k, P);
+    geo = make_float4(0.5f * fmaf(px, px, fmaf(py, py, pz * pz)), 0.5f * fmaf(mx, mx, fmaf(my, my, mz * mz)),
+                      fmaf(u.w, u.w, fmaf(v.w, v.w, w3.rw2)), 0.f);
+    F2 = fu.x * fv.x * w3.fw;  // three cutoffs
   };
   // this lane's factors of one triplet: angle terms A_(4u+li) and radius
   // terms R_(4v+li) F2
   auto lane_factors = [&](const float4& q4, float f2, float (&A)[NP], float (&R)[NQ]) {
-    if constexpr (ZC == kZcBP) {
-      // 2^(2 - zeta) (1 + lambda cos)^zeta and exp(-eta s2) fc fc fc
+    // 2^(2 - zeta) (1 + lambda cos)^zeta and exp(-eta s2) fc fc fc
 #pragma unroll
-      for (int u = 0; u < NP; ++u) A[u] = xa[u] * ipow_rt(xb[u] > 0.f ? q4.x : q4.y, zexp[u], P.bp_zbits);
+    for (int u = 0; u < NP; ++u) A[u] = xa[u] * ipow_rt(xb[u] > 0.f ? q4.x : q4.y, zexp[u], P.bp_zbits);
 #pragma unroll
-      for (int v = 0; v < NQ; ++v) R[v] = fexp2(-rsq[v] * q4.z) * f2;
-    } else {
-      float x[NP];
-#pragma unroll
-      for (int u = 0; u < NP; ++u) x[u] = fmaf(q4.x, xa[u], fmaf(q4.y, xb[u], P.x_c));
-      ipow_sel<(ZC > 0 ? ZC : 0), NP>(x, P.zeta, A);
-#pragma unroll
-      for (int v = 0; v < NQ; ++v) {
-        const float dq = (q4.z - rsq[v]) + (q4.w - rsq_lo[v]);
-        R[v] = fexp2(-eta_a2 * dq * dq) * f2;
-      }
-    }
+    for (int v = 0; v < NQ; ++v) R[v] = fexp2(-rsq[v] * q4.z) * f2;
   };
   // triplet t of species-pair block (a, b), m = na (a == b) or nbb (a < b):
   // a == b numbers the unordered pairs {j, (j + s) mod na} as (s - 1) na + j,
@@ -670,10 +488,10 @@ __device__ __forceinline__ void desc_fwd_atom(int64_t i, bool list_ok, const nn_
   // i supplying A_(4u+i) and R_(4v+i) F2 of each, so that the block's
   // accumulators end up holding exactly that pair block's bins: no
   // reduction across lanes.  The four lanes of a block form each of its
-  // triplets' geometry themselves, except for the BP term (whose third side
-  // is an FP64 computation) with at most 64 triplets: then each lane first
-  // forms one triplet's geometry (numbered block after block) into LDS and
-  // the blocks read it back.
+  // triplets' geometry themselves, except with at most 64 triplets: then
+  // each lane first forms one triplet's geometry (numbered block after
+  // block; the third side is an FP64 computation) into LDS and the blocks
+  // read it back.
   const int nblk = S * (S + 1) / 2;
   const int Tall = nb.n * (nb.n - 1) / 2;
   if (WPA == 1 && nblk > 1 && nblk <= 16 && Tall <= kFuseTriplets) {
@@ -689,7 +507,7 @@ __device__ __forceinline__ void desc_fwd_atom(int64_t i, bool list_ok, const nn_
     for (int o = 32; o >= 1; o >>= 1) Tmax = max(Tmax, __shfl_xor(Tmax, o));
     const int m = pa == pb ? na : nbb;
     const float inv_m = m > 0 ? 1.0f / (float)m : 0.f;
-    const bool staged = ZC == kZcBP && Tall <= kWave;
+    const bool staged = Tall <= kWave;
     int base = 0;  // first triplet of this lane's block in the block-after-block numbering
     if (staged) {
       float4 geo = make_float4(1.f, 0.f, 0.f, 0.f);
@@ -825,17 +643,7 @@ __device__ __forceinline__ void desc_fwd_atom(int64_t i, bool list_ok, const nn_
   }
 }
 
-// With one species the descriptor launch also writes the identity grouping.
-__device__ __forceinline__ void identity_group(IdentityGroup one, const nn_system& sys, int64_t i, int64_t* meta) {
-  one.perm[i] = (int32_t)i;
-  if (sys.species[i] != 0) atomicOr((unsigned long long*)&meta[kMetaErr], (unsigned long long)kErrSpecies);
-  if (i == 0) {
-    one.sp_start[0] = 0;
-    one.sp_start[1] = sys.n_atoms;
-  }
-}
-
-template <int NT, int NRA, int WPA, int ZC>
+template <int NT, int NRA, int WPA>
 __global__ void __launch_bounds__(64 * WPA) k_desc_fwd(nn_system sys, const int64_t* __restrict__ offsets,
                                                        const int32_t* __restrict__ nbr,
                                                        const int8_t* __restrict__ shift, DescConst P,
@@ -845,33 +653,7 @@ __global__ void __launch_bounds__(64 * WPA) k_desc_fwd(nn_system sys, const int6
   const int64_t i = atom_of_block(order, sys.n_atoms, list_ok);
   if (i < 0) return;
   if (one.perm && threadIdx.x == 0) identity_group(one, sys, i, meta);
-  desc_fwd_atom<NT, NRA, WPA, ZC>(i, list_ok, sys, offsets, nbr, shift, P, G, meta);
-}
-
-// The atoms a packed launch leaves out (rows over kPackNb entries), one
-// wave per block of 64 atom slots: the lanes test their slots' rows and the
-// wave then takes the long ones one after another.  Also writes the
-// identity grouping of all atoms.  Nothing else to do while the list is not
-// valid (the packed launch zeroes every row then).
-template <int NT, int NRA, int ZC>
-__global__ void __launch_bounds__(64) k_desc_fwd_long(nn_system sys, const int64_t* __restrict__ offsets,
-                                                      const int32_t* __restrict__ nbr,
-                                                      const int8_t* __restrict__ shift, DescConst P,
-                                                      float* __restrict__ G, int64_t* meta, IdentityGroup one,
-                                                      const int32_t* __restrict__ order) {
-  const bool list_ok = meta[kMetaValid] == 1;
-  const int64_t slot = (int64_t)blockIdx.x * kWave + threadIdx.x;
-  const bool in = slot < sys.n_atoms;
-  const int64_t i = !in ? -1 : (order && list_ok) ? (int64_t)order[slot] : slot;
-  if (one.perm && in) identity_group(one, sys, i, meta);
-  if (!list_ok) return;
-  uint64_t m = __ballot(in && offsets[i + 1] - offsets[i] > kPackNb);
-  while (m) {
-    const int b = __ffsll((unsigned long long)m) - 1;
-    m &= m - 1;
-    desc_fwd_atom<NT, NRA, 1, ZC>(__shfl(i, b), true, sys, offsets, nbr, shift, P, G, meta);
-    __syncthreads();  // this atom's LDS reads are done before the next one's staging
-  }
+  desc_fwd_atom<NT, NRA, WPA>(i, list_ok, sys, offsets, nbr, shift, P, G, meta);
 }
 
 // Directional derivative of the descriptors along a displacement field v
@@ -1201,12 +983,8 @@ __global__ void __launch_bounds__(64 * WPA) k_desc_tan(nn_system sys, const int6
 }
 
 // Per-pair energy gradients dE_i/dd_e (float4 per entry, w unused) from
-// lambda_i = dE_i/dG_i.
-// Floats of the adjoint's radial lambda in LDS: S n_rad rounded up to a
-// multiple of 4, so that the angular blocks after it are float4-aligned.
-__host__ __device__ constexpr int adj_lam_radial(int S, int n_rad) { return (S * n_rad + 3) / 4 * 4; }
-
-template <int NT, int NRA, bool ONE_SPECIES, int WPA, int ZC>
+// lambda_i = dE_i/dG_i, BP term.
+template <int NT, int NRA, bool ONE_SPECIES, int WPA>
 __device__ __forceinline__ void desc_adj_atom(int64_t i, const nn_system& sys, const int64_t* __restrict__ offsets,
                                               const int32_t* __restrict__ nbr, const int8_t* __restrict__ shift,
                                               const DescConst& P, const float* __restrict__ lambda,
@@ -1257,7 +1035,6 @@ __device__ __forceinline__ void desc_adj_atom(int64_t i, const nn_system& sys, c
   for (int t = lane; t < n; t += kWave) gxyz[wv][t] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
   const float eta_r2 = P.eta_rad * 1.4426950408889634f;
-  const float eta_a2 = P.eta_ang * 1.4426950408889634f;
   // radial: lane <-> neighbor (waves take alternate chunks); dE/dd = (dE/dr) d/r
   for (int t0 = wv * kWave; t0 < n; t0 += kWave * WPA) {
     const int t = t0 + lane;
@@ -1277,12 +1054,6 @@ __device__ __forceinline__ void desc_adj_atom(int64_t i, const nn_system& sys, c
       gxyz[wv][t] = a;
     }
   }
-  const int zeta1 = P.zeta - 1;
-  const float zf = (float)P.zeta;
-  const float sq_eta_a2 = sqrtf(eta_a2);
-  float rs_sc[NRA];
-#pragma unroll
-  for (int q = 0; q < NRA; ++q) rs_sc[q] = P.rs_ang[q] * sq_eta_a2;
   // angular: the unordered pairs {j, (j + s) mod n} for s = 1 .. n/2 (for
   // even n the step n/2 only for j < n/2), numbered t = (s - 1) n + j and
   // taken 64 at a time (wave w: chunks w, w + WPA, ...), so every lane has a
@@ -1300,7 +1071,7 @@ __device__ __forceinline__ void desc_adj_atom(int64_t i, const nn_system& sys, c
     int k = j + sj_step;
     if (k >= n) k -= n;
     float gjx = 0.f, gjy = 0.f, gjz = 0.f, gkx = 0.f, gky = 0.f, gkz = 0.f;
-    if (take && ZC == kZcBP) {
+    if (take) {
       // standard BP: E_t = F3 sum_q R_q T_q with R_q = exp(-eta_q s2),
       // T_q = sum_p lambda_qp A_p, A_p = pref_p (1 + lam_p cos)^zeta_p
       const float4 u = nb.d[j], fu = nb.f[j];
@@ -1354,80 +1125,6 @@ __device__ __forceinline__ void desc_adj_atom(int64_t i, const nn_system& sys, c
       gkx = cv * (u.x - g.c * v.x) + two_ds2 * fmaf(v.w, v.x, g.wx) + fk * v.x + fwv * g.wx;
       gky = cv * (u.y - g.c * v.y) + two_ds2 * fmaf(v.w, v.y, g.wy) + fk * v.y + fwv * g.wy;
       gkz = cv * (u.z - g.c * v.z) + two_ds2 * fmaf(v.w, v.z, g.wz) + fk * v.z + fwv * g.wz;
-    } else if (take) {
-      const float4 u = nb.d[j], fu = nb.f[j];
-      const float4 v = nb.d[k], fv = nb.f[k];
-      const float* La = lam_a;
-      if (!ONE_SPECIES) La = lam_a + pair_block(S, nb_species(fu), nb_species(fv)) * NBP;
-      const float4* La4 = reinterpret_cast<const float4*>(La);  // NBP and the block base are multiples of 4
-      const float iru = nb.ir[j], irv = nb.ir[k];
-      const TripGeom g = triplet_geom<false>(u, fu, v, fv, P.eps_ang);
-      const float c = g.c;
-      const float F2 = 2.0f * fu.x * fv.x;
-      float x[NT], P1[NT], A[NT];
-#pragma unroll
-      for (int p = 0; p < NT; ++p) x[p] = fmaf(c, P.x_a[p], fmaf(g.ssm, P.x_b[p], P.x_c));
-      ipow_sel<(ZC > 0 ? ZC - 1 : 0), NT>(x, zeta1, P1);
-#pragma unroll
-      for (int p = 0; p < NT; ++p) A[p] = P1[p] * x[p];
-      // R_q = 2^(-dq_q^2) with dq_q = sqrt(eta log2 e) (rbar - Rs'_q); the
-      // hi/lo split of rbar and Rs' that the forward pass keeps for the
-      // descriptor values is below what the gradient needs
-      float R[NRA], dq[NRA];
-      const float rb = g.rbar * sq_eta_a2;
-#pragma unroll
-      for (int q = 0; q < NRA; ++q) {
-        dq[q] = rb - rs_sc[q];
-        R[q] = fexp2(-dq[q] * dq[q]);
-      }
-      float Tq[NRA], U[NT];
-#pragma unroll
-      for (int p = 0; p < NT; ++p) U[p] = 0.f;
-#pragma unroll
-      for (int q = 0; q < NRA; ++q) {
-        float tq = 0.f;
-#pragma unroll
-        for (int p4 = 0; p4 < NT / 4; ++p4) {
-          const float4 l4 = La4[q * (NT / 4) + p4];  // LDS (a broadcast with one species)
-          const float l[4] = {l4.x, l4.y, l4.z, l4.w};
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int p = 4 * p4 + c;
-            tq = fmaf(l[c], A[p], tq);
-            U[p] = fmaf(l[c], R[q], U[p]);
-          }
-        }
-        Tq[q] = tq;
-      }
-      // E_t = F2 sum_q R_q T_q, T_q = sum_p lambda_qp A_p
-      float dEdF2 = 0.f, dEdravg = 0.f;
-#pragma unroll
-      for (int q = 0; q < NRA; ++q) {
-        dEdF2 = fmaf(Tq[q], R[q], dEdF2);
-        dEdravg = fmaf(Tq[q] * R[q], dq[q], dEdravg);
-      }
-      dEdravg *= -2.0f * P.eta_ang / sq_eta_a2 * F2;
-      float dEdc = 0.f, dEdssm = 0.f;
-#pragma unroll
-      for (int p = 0; p < NT; ++p) {
-        const float gp = U[p] * P1[p];
-        dEdc = fmaf(gp, P.x_a[p], dEdc);
-        dEdssm = fmaf(gp, P.x_b[p], dEdssm);
-      }
-      dEdc *= zf * F2;
-      dEdssm *= zf * F2;
-      // sin^2 = 1 - cos^2, so d ssm / d cos = -cos / ssm
-      const float coef = dEdc - dEdssm * c * frcp(g.ssm);
-      const float dEdru = 0.5f * dEdravg + dEdF2 * 2.0f * fu.y * fv.x;
-      const float dEdrv = 0.5f * dEdravg + dEdF2 * 2.0f * fu.x * fv.y;
-      // d cos / d d_u = (v^ - cos u^) / r_u
-      const float cu = coef * iru, cv = coef * irv;
-      gjx = cu * (v.x - c * u.x) + dEdru * u.x;
-      gjy = cu * (v.y - c * u.y) + dEdru * u.y;
-      gjz = cu * (v.z - c * u.z) + dEdru * u.z;
-      gkx = cv * (u.x - c * v.x) + dEdrv * v.x;
-      gky = cv * (u.y - c * v.y) + dEdrv * v.y;
-      gkz = cv * (u.z - c * v.z) + dEdrv * v.z;
     }
     // steps present in this chunk: from lane 0's to the last taking lane's
     const int last = min(kWave - 1, T - 1 - t0);
@@ -1465,7 +1162,7 @@ __device__ __forceinline__ void desc_adj_atom(int64_t i, const nn_system& sys, c
   }
 }
 
-template <int NT, int NRA, bool ONE_SPECIES, int WPA, int ZC>
+template <int NT, int NRA, bool ONE_SPECIES, int WPA>
 __global__ void __launch_bounds__(64 * WPA) k_desc_adj(nn_system sys, const int64_t* __restrict__ offsets,
                                                        const int32_t* __restrict__ nbr,
                                                        const int8_t* __restrict__ shift, DescConst P,
@@ -1474,28 +1171,7 @@ __global__ void __launch_bounds__(64 * WPA) k_desc_adj(nn_system sys, const int6
   if (meta[kMetaValid] != 1) return;  // no valid list: the gather writes zero forces
   const int64_t i = atom_of_block(order, sys.n_atoms, true);
   if (i < 0) return;
-  desc_adj_atom<NT, NRA, ONE_SPECIES, WPA, ZC>(i, sys, offsets, nbr, shift, P, lambda, pg, meta);
-}
-
-// The atoms a packed adjoint leaves out (rows over kPackNb entries), as in
-// k_desc_fwd_long.
-template <int NT, int NRA, bool ONE_SPECIES, int ZC>
-__global__ void __launch_bounds__(64) k_desc_adj_long(nn_system sys, const int64_t* __restrict__ offsets,
-                                                      const int32_t* __restrict__ nbr,
-                                                      const int8_t* __restrict__ shift, DescConst P,
-                                                      const float* __restrict__ lambda, float4* __restrict__ pg,
-                                                      int64_t* meta, const int32_t* __restrict__ order) {
-  if (meta[kMetaValid] != 1) return;
-  const int64_t slot = (int64_t)blockIdx.x * kWave + threadIdx.x;
-  const bool in = slot < sys.n_atoms;
-  const int64_t i = !in ? -1 : order ? (int64_t)order[slot] : slot;
-  uint64_t m = __ballot(in && offsets[i + 1] - offsets[i] > kPackNb);
-  while (m) {
-    const int b = __ffsll((unsigned long long)m) - 1;
-    m &= m - 1;
-    desc_adj_atom<NT, NRA, ONE_SPECIES, 1, ZC>(__shfl(i, b), sys, offsets, nbr, shift, P, lambda, pg, meta);
-    __syncthreads();
-  }
+  desc_adj_atom<NT, NRA, ONE_SPECIES, WPA>(i, sys, offsets, nbr, shift, P, lambda, pg, meta);
 }
 
 // ---------------------------------------------------------------------------
@@ -1665,7 +1341,7 @@ static inline size_t packed_fwd_lds(int S, int NB) {
 }
 
 // Descriptor rows of kPackAtoms atoms per one-wave block, for atoms whose
-// rows have at most kPackNb entries (k_desc_fwd_long takes the others).
+// rows have at most kPackNb entries (k_fwd_tiles_long takes the others).
 // The radial bins as in k_desc_fwd with one wave, 16 lanes per atom.  The
 // angular bins: the wave's triplets are numbered species-pair block after
 // block, atom after atom (one segment per atom and block), and the 16 4-lane
@@ -1975,7 +1651,7 @@ __host__ __device__ inline int packed_lam_stride(int S, int n_rad, int NB) {
 }
 
 // Per-pair energy gradients for kPackAtoms atoms per one-wave block (rows
-// of at most kPackNb entries; k_desc_adj_long takes the others).  Staging
+// of at most kPackNb entries; k_adj_tiles_long takes the others).  Staging
 // and the radial terms take 16 lanes per atom (lane <-> neighbor).  The
 // triplets of the four atoms are numbered as in k_desc_adj, atom after
 // atom, and taken 64 at a time, one per lane, with the same arithmetic.
@@ -2260,13 +1936,24 @@ bool packed_supported(const DescConst& P) {
   return packed_fwd_lds(P.S, NB) <= 48 * 1024 && adj <= 48 * 1024;
 }
 
-// Waves per atom: two when the atoms alone would leave the SIMDs with few
-// waves to switch between, one otherwise; the packed passes for short rows
-// (small molecules: at most 24 list entries per atom on average).  MLP: the
-// row-block kernel.
+// Waves per atom.  Forward: one, except that the few atoms of a small system
+// leave the chip waiting for single waves (one species, 52 neighbors: four
+// waves 20 us, two 23, one 33 at 1024 atoms; 50, 47 and 53 at 4096; 91, 79
+// and 80 at 8192); three or more species have short species-pair blocks that
+// more waves cannot share (four species: one wave 71, two 82 us at 4096
+// atoms).  Adjoint: two, which share an atom's records in LDS and so keep
+// more waves resident than one (one species: 341 against 409 us at 32768
+// atoms), four up to 8192 atoms (60 against 65 us at 4096).  The packed passes for short
+// rows (small molecules: at most 24 list entries per atom on average).  MLP:
+// the row-block kernel.
 LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity) {
-  const int w = n_atoms <= 16384 ? 2 : 1;
+  const bool bp = P.kind == NN_DESC_BP;
+  const int w = n_atoms <= 16384 ? 2 : 1;  // the BP term's passes
   LaunchPlan plan{w, w, 1};  // the row-block MLP where it takes the shape (FP32), else the tile kernel's default
+  if (!bp) {
+    plan.wpa_fwd = n_atoms <= 1024 ? 4 : n_atoms <= (P.S >= 3 ? 2048 : 8192) ? 2 : 1;
+    plan.wpa_adj = n_atoms <= 8192 ? 4 : 2;
+  }
   const bool short_rows = n_atoms > 0 && capacity <= 24 * n_atoms;
   if (short_rows && packed_supported(P)) {
     plan.wpa_fwd = plan.wpa_adj = 0;
@@ -2278,10 +1965,10 @@ LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity) {
   return plan;
 }
 
-template <int NT, int NRA, int WPA, int ZC>
+template <int NT, int NRA, int WPA>
 static void launch_fwd_w(const nn_system& sys, const nn_nlist& nl, const DescConst& P, float* G, IdentityGroup one,
                          hipStream_t s) {
-  hipLaunchKernelGGL((k_desc_fwd<NT, NRA, WPA, ZC>), dim3(atom_grid(sys.n_atoms, nl.order)), dim3(64 * WPA), 0, s,
+  hipLaunchKernelGGL((k_desc_fwd<NT, NRA, WPA>), dim3(atom_grid(sys.n_atoms, nl.order)), dim3(64 * WPA), 0, s,
                      sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
 }
 
@@ -2292,8 +1979,7 @@ static void launch_fwd_packed(const nn_system& sys, const nn_nlist& nl, const De
                               IdentityGroup one, hipStream_t s) {
   hipLaunchKernelGGL((k_desc_fwd_packed<NT, NRA, ZC>), dim3(packed_grid(sys.n_atoms)), dim3(64),
                      packed_fwd_lds(P.S, NT * NRA), s, sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta);
-  hipLaunchKernelGGL((k_desc_fwd_long<NT, NRA, ZC>), dim3((unsigned)((sys.n_atoms + kWave - 1) / kWave)), dim3(64), 0,
-                     s, sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
+  launch_fwd_tiles(sys, nl, P, G, one, 0, s);
 }
 
 template <int NT, int NRA>
@@ -2305,17 +1991,11 @@ static void launch_fwd_t(const nn_system& sys, const nn_nlist& nl, const DescCon
     return;
   }
   if (P.kind == NN_DESC_BP) {
-    if (wpa == 4) launch_fwd_w<NT, NRA, 4, kZcBP>(sys, nl, P, G, one, s);
-    else if (wpa == 2) launch_fwd_w<NT, NRA, 2, kZcBP>(sys, nl, P, G, one, s);
-    else launch_fwd_w<NT, NRA, 1, kZcBP>(sys, nl, P, G, one, s);
-  } else if (P.zeta == 50) {
-    if (wpa == 4) launch_fwd_w<NT, NRA, 4, 50>(sys, nl, P, G, one, s);
-    else if (wpa == 2) launch_fwd_w<NT, NRA, 2, 50>(sys, nl, P, G, one, s);
-    else launch_fwd_w<NT, NRA, 1, 50>(sys, nl, P, G, one, s);
+    if (wpa == 4) launch_fwd_w<NT, NRA, 4>(sys, nl, P, G, one, s);
+    else if (wpa == 2) launch_fwd_w<NT, NRA, 2>(sys, nl, P, G, one, s);
+    else launch_fwd_w<NT, NRA, 1>(sys, nl, P, G, one, s);
   } else {
-    if (wpa == 4) launch_fwd_w<NT, NRA, 4, 0>(sys, nl, P, G, one, s);
-    else if (wpa == 2) launch_fwd_w<NT, NRA, 2, 0>(sys, nl, P, G, one, s);
-    else launch_fwd_w<NT, NRA, 1, 0>(sys, nl, P, G, one, s);
+    launch_fwd_tiles(sys, nl, P, G, one, wpa == 0 ? 1 : wpa, s);
   }
 }
 
@@ -2344,12 +2024,12 @@ static void launch_tan_t(const nn_system& sys, const nn_nlist& nl, const DescCon
   }
 }
 
-template <int NT, int NRA, bool ONE, int WPA, int ZC>
+template <int NT, int NRA, bool ONE, int WPA>
 static void launch_adj_w(const nn_system& sys, const nn_nlist& nl, const DescConst& P, const float* lam, float4* pg,
                          hipStream_t s) {
   const size_t lds =
       sizeof(float) * ((size_t)adj_lam_radial(P.S, P.n_rad) + (size_t)(P.S * (P.S + 1) / 2) * (NT * NRA + 4));
-  hipLaunchKernelGGL((k_desc_adj<NT, NRA, ONE, WPA, ZC>), dim3(atom_grid(sys.n_atoms, nl.order)), dim3(64 * WPA), lds,
+  hipLaunchKernelGGL((k_desc_adj<NT, NRA, ONE, WPA>), dim3(atom_grid(sys.n_atoms, nl.order)), dim3(64 * WPA), lds,
                      s, sys, nl.offsets, nl.nbr, nl.shift, P, lam, pg, nl.meta, nl.order);
 }
 
@@ -2359,10 +2039,7 @@ static void launch_adj_packed(const nn_system& sys, const nn_nlist& nl, const De
   const size_t lds = sizeof(float) * kPackAtoms * packed_lam_stride(P.S, P.n_rad, NT * NRA);
   hipLaunchKernelGGL((k_desc_adj_packed<NT, NRA, ONE, ZC>), dim3(packed_grid(sys.n_atoms)), dim3(64), lds, s, sys,
                      nl.offsets, nl.nbr, nl.shift, P, lam, pg, nl.meta);
-  const size_t lds1 =
-      sizeof(float) * ((size_t)adj_lam_radial(P.S, P.n_rad) + (size_t)(P.S * (P.S + 1) / 2) * (NT * NRA + 4));
-  hipLaunchKernelGGL((k_desc_adj_long<NT, NRA, ONE, ZC>), dim3((unsigned)((sys.n_atoms + kWave - 1) / kWave)),
-                     dim3(64), lds1, s, sys, nl.offsets, nl.nbr, nl.shift, P, lam, pg, nl.meta, nl.order);
+  launch_adj_tiles(sys, nl, P, lam, pg, 0, s);
 }
 
 template <int NT, int NRA, bool ONE>
@@ -2374,17 +2051,11 @@ static void launch_adj_o(const nn_system& sys, const nn_nlist& nl, const DescCon
     return;
   }
   if (P.kind == NN_DESC_BP) {
-    if (wpa == 4) launch_adj_w<NT, NRA, ONE, 4, kZcBP>(sys, nl, P, lam, pg, s);
-    else if (wpa == 2) launch_adj_w<NT, NRA, ONE, 2, kZcBP>(sys, nl, P, lam, pg, s);
-    else launch_adj_w<NT, NRA, ONE, 1, kZcBP>(sys, nl, P, lam, pg, s);
-  } else if (P.zeta == 50) {
-    if (wpa == 4) launch_adj_w<NT, NRA, ONE, 4, 50>(sys, nl, P, lam, pg, s);
-    else if (wpa == 2) launch_adj_w<NT, NRA, ONE, 2, 50>(sys, nl, P, lam, pg, s);
-    else launch_adj_w<NT, NRA, ONE, 1, 50>(sys, nl, P, lam, pg, s);
+    if (wpa == 4) launch_adj_w<NT, NRA, ONE, 4>(sys, nl, P, lam, pg, s);
+    else if (wpa == 2) launch_adj_w<NT, NRA, ONE, 2>(sys, nl, P, lam, pg, s);
+    else launch_adj_w<NT, NRA, ONE, 1>(sys, nl, P, lam, pg, s);
   } else {
-    if (wpa == 4) launch_adj_w<NT, NRA, ONE, 4, 0>(sys, nl, P, lam, pg, s);
-    else if (wpa == 2) launch_adj_w<NT, NRA, ONE, 2, 0>(sys, nl, P, lam, pg, s);
-    else launch_adj_w<NT, NRA, ONE, 1, 0>(sys, nl, P, lam, pg, s);
+    launch_adj_tiles(sys, nl, P, lam, pg, wpa == 0 ? 1 : wpa, s);
   }
 }
 
@@ -2399,15 +2070,6 @@ bool desc_supported(int nt, int nra) {
   return (nt == 4 || nt == 8 || nt == 16) && (nra == 4 || nra == 8) && nt * nra <= 128;
 }
 
-#define NNP_DISPATCH(NT_, NRA_, CALL)                                          \
-  do {                                                                         \
-    if (nt == 4 && nra == 4) { constexpr int NT_ = 4, NRA_ = 4; CALL; }        \
-    else if (nt == 4 && nra == 8) { constexpr int NT_ = 4, NRA_ = 8; CALL; }   \
-    else if (nt == 8 && nra == 4) { constexpr int NT_ = 8, NRA_ = 4; CALL; }   \
-    else if (nt == 8 && nra == 8) { constexpr int NT_ = 8, NRA_ = 8; CALL; }   \
-    else if (nt == 16 && nra == 4) { constexpr int NT_ = 16, NRA_ = 4; CALL; } \
-    else if (nt == 16 && nra == 8) { constexpr int NT_ = 16, NRA_ = 8; CALL; } \
-  } while (0)
 
 void launch_desc_fwd(const nn_system& sys, const nn_nlist& nl, const DescConst& P, float* G, IdentityGroup one,
                      int wpa, hipStream_t s) {
