@@ -251,7 +251,7 @@ bool mlp_supported(int h1, int h2);
 // mode 0 FP32, 1 BF16, 2 split BF16; waves per tile 4 or 8 (0: default)
 void launch_mlp(const MlpArgs& a, int h1, int h2, int mode, int64_t N, int waves, hipStream_t s);
 // mlp_rows.hip: the FP32 row-block MLP (64 atoms per block, weights staged in
-// LDS); shapes (64, 32) and (128, 128) with D a multiple of 4
+// LDS; 16 atoms per block for few atoms); shapes (64, 32) and (128, 128) with D a multiple of 4
 bool mlp_rows_supported(int h1, int h2, int D);
 void launch_mlp_rows(const MlpArgs& a, int h1, int h2, int64_t N, hipStream_t s);
 // its BF16 modes (mode 1 plain, 2 split; the BF16 weight copies prepared),

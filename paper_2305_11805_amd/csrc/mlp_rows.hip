@@ -624,8 +624,22 @@ bool mlp_rows_supported(int h1, int h2, int D) {
   return ((h1 == 64 && h2 == 32) || (h1 == 128 && h2 == 128)) && D % 4 == 0;
 }
 
+// Below this many atoms a block takes 16 of them instead of 64, its four
+// waves sharing the columns of each product (the tile kernel): 64-atom blocks
+// would leave most CUs without one, and a block's time is then its own chain
+// of weight loads.  MLP time in us, 64 against 16 atoms a block:
+//   64-32, D 384, 4 species    192 atoms  31 / 18    8516  37 / 36   17310  47 / 54
+//   128-128, D 96, 1 species  4096 atoms  37 / 17   12288  45 / 40   16384  44 / 43
+//   128-128, D 768, 4 species 4096 atoms 107 / 43   12288 109 / 112  16384 108 / 134
+//   64-32, D 152, 1 species    256 atoms  19 / 13   12288  22 / 20   16384  22 / 29
+constexpr int64_t kRowsMin = 12288;
+
 void launch_mlp_rows(const MlpArgs& a, int h1, int h2, int64_t N, hipStream_t s) {
   if (N == 0) return;
+  if (N < kRowsMin) {
+    launch_mlp(a, h1, h2, 0, N, 4, s);
+    return;
+  }
   const unsigned grid = (unsigned)((N + kRwAtoms - 1) / kRwAtoms + a.model.S);
   if (h1 == 64 && h2 == 32) {
     constexpr size_t lds = RowsShape<4, 2>::lds;
