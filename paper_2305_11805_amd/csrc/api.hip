@@ -1265,7 +1265,9 @@ nn_status nn_energy_forces_qeq(const nn_system* sys, const nn_nlist* nl, const n
     StageTimer t(NN_STAGE_MLP, s);
     launch_mlp_layers_outputs(la, N, s);
   }
-  launch_qeq_solve(qa, s);
+  // the Coulomb forces take the place of the network outputs they came from
+  float* Fc = F ? L.qeq_out : nullptr;
+  launch_qeq_solve(qa, Fc, s);
   if (F) {
     {
       StageTimer t(NN_STAGE_MLP, s);
@@ -1276,8 +1278,7 @@ nn_status nn_energy_forces_qeq(const nn_system* sys, const nn_nlist* nl, const n
       launch_desc_adj(*sys, *nl, P, L.lam, L.pg, plan.wpa_adj, s);
     }
     StageTimer t(NN_STAGE_FORCE_GATHER, s);
-    launch_force_gather(*sys, *nl, L.pg, F, EnergyJob{nullptr, sys->atom_ptr, 0, nullptr}, s);
-    launch_qeq_coulomb(qa, F, s);
+    launch_force_gather(*sys, *nl, L.pg, F, EnergyJob{nullptr, sys->atom_ptr, 0, nullptr}, s, Fc);
   }
   return check_launch("nn_energy_forces_qeq");
 }

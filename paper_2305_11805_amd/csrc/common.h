@@ -201,8 +201,9 @@ struct EnergyJob {  // per-structure energy sums run by extra blocks of the gath
   int32_t B;
   double* E_struct;
 };
+// F += Fc [N][3] if Fc is not null
 void launch_force_gather(const nn_system& sys, const nn_nlist& nl, const float4* pg, float* F, const EnergyJob& ej,
-                         hipStream_t s);
+                         hipStream_t s, const float* Fc = nullptr);
 size_t jacobian_floats(int n_rad, int S, int nt, int nra, int64_t capacity);
 void launch_desc_jac(const nn_system& sys, const nn_nlist& nl, const DescConst& P, float* J, hipStream_t s);
 void launch_jac_contract(const nn_system& sys, const nn_nlist& nl, const DescConst& P, const float* lam,
@@ -331,9 +332,8 @@ struct QeqArgs {
   float* seed;              // [N][3] (1, q, q^2 / 2)
   int64_t* meta;            // error bits
 };
-void launch_qeq_solve(const QeqArgs& a, hipStream_t s);
-// F [N][3] += the Coulomb pair forces at the charges a.q
-void launch_qeq_coulomb(const QeqArgs& a, float* F, hipStream_t s);
+// Fc [N][3] (null: not wanted) receives the Coulomb pair forces; it may be a.out
+void launch_qeq_solve(const QeqArgs& a, float* Fc, hipStream_t s);
 
 // wgrad.hip
 struct WgradArgs {

@@ -1886,7 +1886,8 @@ __global__ void __launch_bounds__(64) k_desc_adj_packed(nn_system sys, const int
 __global__ void __launch_bounds__(256) k_force_gather(int64_t N, const int64_t* __restrict__ offsets,
                                                       const int32_t* __restrict__ rev, const float4* __restrict__ pg,
                                                       const int32_t* __restrict__ order, float* __restrict__ F,
-                                                      const int64_t* meta, unsigned n_gather_blocks, EnergyJob ej) {
+                                                      const int64_t* meta, unsigned n_gather_blocks, EnergyJob ej,
+                                                      const float* __restrict__ Fc) {
   if (blockIdx.x >= n_gather_blocks) {
     energy_block_sum(ej.E_atom, ej.atom_ptr, N, (int)(blockIdx.x - n_gather_blocks), ej.E_struct);
     return;
@@ -1918,6 +1919,11 @@ __global__ void __launch_bounds__(256) k_force_gather(int64_t N, const int64_t* 
     fz += __shfl_xor(fz, m, 16);
   }
   if (sub == 0 && slot < N) {
+    if (Fc) {
+      fx += Fc[3 * k];
+      fy += Fc[3 * k + 1];
+      fz += Fc[3 * k + 2];
+    }
     F[3 * k] = fx;
     F[3 * k + 1] = fy;
     F[3 * k + 2] = fz;
@@ -2095,12 +2101,12 @@ void launch_desc_tan(const nn_system& sys, const nn_nlist& nl, const DescConst& 
 // F from the per-entry gradients; blocks past the gather's sum the
 // per-structure energies (ej.B of them) in the same launch.
 void launch_force_gather(const nn_system& sys, const nn_nlist& nl, const float4* pg, float* F, const EnergyJob& ej,
-                         hipStream_t s) {
+                         hipStream_t s, const float* Fc) {
   unsigned ng = (unsigned)((sys.n_atoms * 16 + 255) / 256);
   if (nl.order) ng = (ng + 7) / 8 * 8;  // whole rounds of the eight XCDs (the extra slots are past N)
   if (ng + (unsigned)ej.B == 0) return;
   hipLaunchKernelGGL(k_force_gather, dim3(ng + (unsigned)ej.B), dim3(256), 0, s, sys.n_atoms, nl.offsets, nl.rev, pg,
-                     nl.order, F, nl.meta, ng, ej);
+                     nl.order, F, nl.meta, ng, ej, Fc);
 }
 
 
