@@ -48,39 +48,53 @@ __global__ void __launch_bounds__(64) k_sp_scatter(const int32_t* __restrict__ s
   if (blockIdx.x == 0 && lane <= S) sp_start[lane] = off[(int64_t)lane * nblk];
 }
 
-// The same grouping in one block for N <= kSpSmall: each thread counts the
-// species of a contiguous run of atoms, the runs' counts are scanned per
-// species, and each thread then places its run.
+// The same grouping in one block for N <= kSpSmall: wave w takes the w-th
+// stretch of atoms, 64 at a time in order, counts each species by ballots,
+// and after a scan of the counts over the waves places its atoms the same
+// way.  Every load is of 64 consecutive atoms and eight are in flight: with a
+// contiguous run of atoms per thread, whose loads touch a line each and
+// follow one another, 8516 atoms took 12 us, now 8, and 4096 took 7, now 5.
+// The line lies where one block's passes over the atoms cost as much as the
+// three launches above: 32768 atoms take 19.5 us here and 14.7 there.
 constexpr int kSpThreads = 1024;
-constexpr int64_t kSpSmall = 64 * 1024;
+constexpr int64_t kSpSmall = 16 * 1024;
+
+template <typename Each>
+__device__ __forceinline__ void sp_walk(const int32_t* __restrict__ species, int64_t b, int64_t e, int lane, Each&& each) {
+  for (int64_t k0 = b; k0 < e; k0 += 8 * 64) {
+    int v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int64_t k = k0 + 64 * r + lane;
+      v[r] = k < e ? species[k] : -1;
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (k0 + 64 * r < e) each(k0 + 64 * r + lane, v[r]);
+  }
+}
 
 __global__ void __launch_bounds__(kSpThreads) k_sp_group_small(const int32_t* __restrict__ species, int64_t N, int S,
                                                                int32_t* __restrict__ perm,
                                                                int64_t* __restrict__ sp_start) {
   constexpr int NW = kSpThreads / 64;
   __shared__ int wtot[NW][NN_MAX_SPECIES];
-  __shared__ int64_t start[NN_MAX_SPECIES + 1];
+  __shared__ int start[NN_MAX_SPECIES + 1];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int64_t per = (N + kSpThreads - 1) / kSpThreads;
-  const int64_t b = (int64_t)t * per, e = min(b + per, N);
-  int cnt[NN_MAX_SPECIES], incl[NN_MAX_SPECIES];
+  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const int64_t chunk = (N + NW * 64 - 1) / (NW * 64) * 64;
+  const int64_t b = min(w * chunk, N), e = min(b + chunk, N);
+  int cnt[NN_MAX_SPECIES];
 #pragma unroll
   for (int q = 0; q < NN_MAX_SPECIES; ++q) cnt[q] = 0;
-  for (int64_t k = b; k < e; ++k) {
-    const int sp = species[k];
+  sp_walk(species, b, e, lane, [&](int64_t, int sp) {
 #pragma unroll
-    for (int q = 0; q < NN_MAX_SPECIES; ++q) cnt[q] += (sp == q && q < S) ? 1 : 0;
-  }
+    for (int q = 0; q < NN_MAX_SPECIES; ++q)
+      if (q < S) cnt[q] += __popcll(__ballot(sp == q));
+  });
+  if (lane == 0)
 #pragma unroll
-  for (int q = 0; q < NN_MAX_SPECIES; ++q) {
-    int x = cnt[q];
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(x, off);
-      if (lane >= off) x += v;
-    }
-    incl[q] = x;
-    if (lane == 63) wtot[w][q] = x;
-  }
+    for (int q = 0; q < NN_MAX_SPECIES; ++q) wtot[w][q] = cnt[q];
   __syncthreads();
   if (t < NN_MAX_SPECIES) {  // thread q: exclusive scan of species q over the waves
     int run = 0;
@@ -97,16 +111,19 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_group_small(const int32_t* __
     for (int q = 0; q < NN_MAX_SPECIES; ++q) start[q + 1] = start[q] + (q < S ? start[q + 1] : 0);
   }
   __syncthreads();
-  int64_t at[NN_MAX_SPECIES];
+  if (t <= S) sp_start[t] = start[t];
+  int at[NN_MAX_SPECIES];
 #pragma unroll
-  for (int q = 0; q < NN_MAX_SPECIES; ++q) at[q] = start[q] + wtot[w][q] + incl[q] - cnt[q];
-  for (int64_t k = b; k < e; ++k) {
-    const int sp = species[k];
+  for (int q = 0; q < NN_MAX_SPECIES; ++q) at[q] = start[q] + wtot[w][q];
+  sp_walk(species, b, e, lane, [&](int64_t k, int sp) {
 #pragma unroll
     for (int q = 0; q < NN_MAX_SPECIES; ++q)
-      if (sp == q && q < S) perm[at[q]++] = (int32_t)k;
-  }
-  if (t <= S) sp_start[t] = start[t];
+      if (q < S) {
+        const uint64_t m = __ballot(sp == q);
+        if (sp == q) perm[at[q] + __popcll(m & lt)] = (int32_t)k;
+        at[q] += __popcll(m);
+      }
+  });
 }
 
 // ---------------------------------------------------------------------------
