@@ -180,20 +180,33 @@ void launch_desc_adj(const nn_system& sys, const nn_nlist& nl, const DescConst& 
 void launch_desc_tan(const nn_system& sys, const nn_nlist& nl, const DescConst& P, const float* v, float* U,
                      int wpa, hipStream_t s);
 // FP64 sum of E_atom over structure c by one block of 256 threads (a fixed
-// tree, so the result is the same on every run).
+// tree, so the result is the same on every run).  A thread's reads follow one
+// another, so sixteen are in flight: with one, a structure of 262144 atoms took
+// 470 us and held up the force gather that this runs beside, one of 32768 42.
 __device__ __forceinline__ void energy_block_sum(const float* __restrict__ E_atom, const int64_t* __restrict__ atom_ptr,
                                                  int64_t N, int c, double* __restrict__ E_struct) {
+  constexpr int kU = 16;
   __shared__ double sh[256];
   const int64_t a0 = min(max(atom_ptr[c], (int64_t)0), N), a1 = min(max(atom_ptr[c + 1], a0), N);
+  const int t = threadIdx.x;
   double acc = 0.0;
-  for (int64_t a = a0 + threadIdx.x; a < a1; a += 256) acc += (double)E_atom[a];
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-    __syncthreads();
+  for (int64_t a = a0 + t; a < a1; a += 256 * kU) {
+    float v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = E_atom[min(a + 256 * u, a1 - 1)];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) acc += a + 256 * u < a1 ? (double)v[u] : 0.0;
   }
-  if (threadIdx.x == 0) E_struct[c] = sh[0];
+  if (a1 - a0 > 64) {
+    sh[t] = acc;
+    __syncthreads();
+    if (t < 128) sh[t] += sh[t + 128];
+    __syncthreads();
+    if (t < 64) acc = sh[t] + sh[t + 64];
+  }
+  if (t >= 64) return;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off);
+  if (t == 0) E_struct[c] = acc;
 }
 struct EnergyJob {  // per-structure energy sums run by extra blocks of the gather
   const float* E_atom;

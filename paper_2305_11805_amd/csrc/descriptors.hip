@@ -1883,20 +1883,29 @@ __global__ void __launch_bounds__(64) k_desc_adj_packed(nn_system sys, const int
 // (b mod 8) * per + b / 8: consecutive blocks go to different XCDs, so each
 // XCD walks one contiguous stretch of the bin order and the neighbor rows
 // its atoms read back stay in its L2.
+//
+// The reads of the reverse entries, 16 bytes of a line each, bound it; their
+// chain rev -> pg is what has to overlap, so a lane has kU entries in flight
+// (262144 atoms of 99 entries, 4.3 GB in lines: 330 us).  Rows of at most 16
+// entries take a lane's one entry alone, where the clamped extra reads cost
+// more than they hide (67000 atoms of 10: 9.0 against 10.7 us).  The
+// energy sums' blocks come first, since one large structure's is a chain.
 __global__ void __launch_bounds__(256) k_force_gather(int64_t N, const int64_t* __restrict__ offsets,
                                                       const int32_t* __restrict__ rev, const float4* __restrict__ pg,
                                                       const int32_t* __restrict__ order, float* __restrict__ F,
                                                       const int64_t* meta, unsigned n_gather_blocks, EnergyJob ej,
                                                       const float* __restrict__ Fc) {
-  if (blockIdx.x >= n_gather_blocks) {
-    energy_block_sum(ej.E_atom, ej.atom_ptr, N, (int)(blockIdx.x - n_gather_blocks), ej.E_struct);
+  constexpr int kU = 4;
+  if ((int)blockIdx.x < ej.B) {
+    energy_block_sum(ej.E_atom, ej.atom_ptr, N, (int)blockIdx.x, ej.E_struct);
     return;
   }
   const bool valid = meta[kMetaValid] == 1;
-  int64_t blk = blockIdx.x;
+  const unsigned b = blockIdx.x - (unsigned)ej.B;
+  int64_t blk = b;
   if (order) {
     const unsigned per = (n_gather_blocks + 7) / 8;
-    blk = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+    blk = (int64_t)(b % 8) * per + b / 8;
   }
   const int64_t slot = ((blk * blockDim.x) + threadIdx.x) >> 4;
   const int sub = threadIdx.x & 15;
@@ -1904,12 +1913,33 @@ __global__ void __launch_bounds__(256) k_force_gather(int64_t N, const int64_t* 
   if (order && valid && slot < N) k = order[slot];
   float fx = 0.f, fy = 0.f, fz = 0.f;
   if (slot < N && valid) {
-    const int64_t e1 = offsets[k + 1];
-    for (int64_t e = offsets[k] + sub; e < e1; e += 16) {
-      const float4 a = pg[e], b = pg[rev[e]];
-      fx += a.x - b.x;
-      fy += a.y - b.y;
-      fz += a.z - b.z;
+    const int64_t e0 = offsets[k], e1 = offsets[k + 1];
+    if (e1 - e0 <= 16) {
+      if (e0 + sub < e1) {
+        const float4 p = pg[e0 + sub], q = pg[rev[e0 + sub]];
+        fx = p.x - q.x;
+        fy = p.y - q.y;
+        fz = p.z - q.z;
+      }
+    } else {
+      for (int64_t e = e0 + sub; e < e1; e += 16 * kU) {
+        int32_t r[kU];
+        float4 p[kU], q[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) r[u] = rev[min(e + 16 * u, e1 - 1)];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          p[u] = pg[min(e + 16 * u, e1 - 1)];
+          q[u] = pg[r[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const bool on = e + 16 * u < e1;
+          fx += on ? p[u].x - q[u].x : 0.f;
+          fy += on ? p[u].y - q[u].y : 0.f;
+          fz += on ? p[u].z - q[u].z : 0.f;
+        }
+      }
     }
   }
 #pragma unroll
