@@ -1,21 +1,40 @@
-// Per-species MLP of Eq. (1) (Sec. II.A), FP32, in row blocks: one block of
-// four waves takes 64 atoms of one species and each wave carries 16 of them
-// through the whole network (both hidden layers, the output, and the
+// Per-species MLP of Eq. (1) (Sec. II.A), FP32, in row blocks: one block
+// takes 16 atoms of one species per wave (4 or 8 waves), and each wave carries
+// its 16 through the whole network (both hidden layers, the output, and the
 // backward pass to lambda = dE/dG).  Every weight block a product needs is
-// staged in LDS once per block and read by the four waves, so the weights
-// are fetched once per 64 atoms; the tile kernel (mlp.hip) splits the
+// staged in LDS once per block and read by all waves, so the weights
+// are fetched once per 64 or 128 atoms; the tile kernel (mlp.hip) splits the
 // hidden units over its waves and fetches them once per 16.
 //
-// Products (16x16x4 FP32 MFMA in the k-permuted form of mma4_f32; C layout:
-// lane (lm, lk) holds rows 4 lk + j, column lm of a 16x16 tile):
+// Products (C layout: lane (lm, lk) holds rows 4 lk + j, column lm of a 16x16
+// tile):
 //   P1  z1 = G W1^T       A: G rows (global), B: W1[:, k0:k0+KC] staged as [n][k]
-//   P2  z2 = a1 W2^T      A: a1 (the wave's LDS rows), B: W2[:, k0:k0+KC] as [n][k]
-//   P3  g1 = delta2 W2    A: delta2 (LDS rows), B: W2[k0:k0+KC, :] staged transposed as [n][k]
-//   P4  lambda = delta1 W1  A: delta1 (LDS rows), B: W1[:, c0:c0+NC] staged transposed as [n][k]
+//   P2  z2 = a1 W2^T      A: a1, B: W2[:, k0:k0+KC] as [n][k]
+//   P3  g1 = delta2 W2    A: delta2, B: W2[k0:k0+KC, :] staged transposed as [n][k]
+//   P4  lambda = delta1 W1  A: delta1, B: W1[:, c0:c0+NC] staged transposed as [n][k]
 // with delta2 = w3 act'(z2), delta1 = g1 act'(z1); E = w3 . a2 + b3.  Sums
 // have a fixed order (k in increasing chunks), so results are the same on
 // every run.
+//
+// A product of FP32 values is taken exactly to 2^-23: each operand splits into
+// three BF16 parts that hold all its 24 bits, and six of the nine products of
+// parts (all above 2^-24 of the whole) go through v_mfma_f32_16x16x32_bf16,
+// whose sums are FP32.  The FP32 matrix instruction does 30 multiply-adds a
+// clock, six BF16 ones 85, and with 32 k an instruction in place of 4 there are
+// fewer roundings: energies and forces against 64 bits 2.0e-6 of their size
+// for 2048 molecules (2.1e-6 with FP32 instructions), 2.3e-6 (2.4e-6) for
+// 32768 atoms of 4 species, 1.8e-6 (1.9e-6) for 262144 of 2.
+//
+// What bounds it: 64-32 networks the traffic of G and lambda (2048 molecules,
+// D 384, 0.21 GB: 94 -> 65 us), read in P1 and written in P4; the wider ones
+// the splitting, the LDS reads and the matrix products of a chunk of 32 k, about
+// equal and overlapping only between waves (128-128, D 768, 32768 atoms 158 ->
+// 113 us; D 288, 262144 atoms 530 -> 297; 256-128, D 152, 16384 atoms, by
+// the tile kernel before, 97 -> 66).  Two chunks in flight instead of one, and
+// 32 atoms a wave instead of 16, were slower.
 #include <math.h>
+
+#include <type_traits>
 
 #include "common.h"
 #include "mlp_ops.h"
@@ -31,45 +50,51 @@ __device__ __forceinline__ void rw_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-template <int H1T, int H2T>
+// W waves of 16 atoms: 4 for 64-32, where blocks are what fills the chip, and
+// for 256-128 (registers); 8 for 128-128, so that a staged block serves 128
+// atoms (262144 atoms: 303 us, with 4 waves 332 to 360).
+template <int H1T, int H2T, int W>
 struct RowsShape {
   static constexpr int H1 = 16 * H1T, H2 = 16 * H2T;
   static constexpr int HM = H1 > H2 ? H1 : H2;
-  static constexpr int KC = 32;   // k (P1-P3) or column (P4) chunk of a staged block (LDS <= 64 KB)
-  static constexpr int LDW = KC + 4;               // staged [n][k] rows of P1-P3
-  static constexpr int LDT = H1 + 4;               // staged [n][k] rows of P4 (k over H1)
-  static constexpr int LDA = HM + 4;               // the wave's activation rows
-  static constexpr int WS1 = HM * LDW, WS4 = KC * LDT;
-  static constexpr int WS = WS1 > WS4 ? WS1 : WS4;  // floats of the staging buffer
-  static constexpr size_t lds = sizeof(float) * ((size_t)WS + (size_t)kRwWaves * 16 * LDA);
+  static constexpr int KC = 32;       // k (P1-P3) or column (P4) chunk of a staged block
+  static constexpr int LDA = KC + 4;  // rows of the wave's 16 x KC exchange tile
+  static constexpr int U1 = HM * KC / 8, U4 = KC * H1 / 8;
+  static constexpr int WSU = U1 > U4 ? U1 : U4;  // 16-byte units (8 values) of one staged part
+  static constexpr size_t lds = 3 * 16 * (size_t)WSU + sizeof(float) * (size_t)W * 16 * LDA;
 };
 
-template <int H1T, int H2T>
-__global__ void __launch_bounds__(64 * kRwWaves) k_mlp_rows(MlpArgs args) {
-  using Sh = RowsShape<H1T, H2T>;
-  constexpr int H1 = Sh::H1, H2 = Sh::H2, KC = Sh::KC, LDW = Sh::LDW, LDT = Sh::LDT, LDA = Sh::LDA;
+struct Split3 {
+  bf16x8 h, m, l;
+};
+
+template <int H1T, int H2T, int W>
+__global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp_rows(MlpArgs args) {
+  using Sh = RowsShape<H1T, H2T, W>;
+  constexpr int NA = 16 * W;  // atoms of a block
+  constexpr int H1 = Sh::H1, H2 = Sh::H2, KC = Sh::KC, LDA = Sh::LDA, WSU = Sh::WSU;
   extern __shared__ float4 rw_lds4[];
-  float* ws = reinterpret_cast<float*>(rw_lds4);
-  __shared__ int32_t rows[kRwAtoms];
+  bf16x8* wst = reinterpret_cast<bf16x8*>(rw_lds4);  // parts h, m, l of WSU units each
+  __shared__ int32_t rows[NA];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float* abuf = ws + Sh::WS + wv * 16 * LDA;  // this wave's rows
+  float* xch = reinterpret_cast<float*>(wst + 3 * WSU) + wv * 16 * LDA;  // this wave's exchange tile
   const int lm = lane & 15, lk = lane >> 4;
-  // which species / block of 64 atoms
+  // which species / block of NA atoms
   const int S = args.model.S;
   int64_t t = blockIdx.x;
   int s = 0;
   int64_t ns = 0;
   for (; s < S; ++s) {
     ns = args.sp_start[s + 1] - args.sp_start[s];
-    const int64_t nt = (ns + kRwAtoms - 1) / kRwAtoms;
+    const int64_t nt = (ns + NA - 1) / NA;
     if (t < nt) break;
     t -= nt;
   }
   if (s >= S) return;
-  const int64_t r0 = args.sp_start[s] + t * kRwAtoms;
-  const int nrows = (int)min<int64_t>(kRwAtoms, args.sp_start[s] + ns - r0);
-  if (tid < kRwAtoms) rows[tid] = tid < nrows ? args.perm[r0 + tid] : -1;
+  const int64_t r0 = args.sp_start[s] + t * NA;
+  const int nrows = (int)min<int64_t>(NA, args.sp_start[s] + ns - r0);
+  if (tid < NA) rows[tid] = tid < nrows ? args.perm[r0 + tid] : -1;
   __syncthreads();
   const MlpDev& M = args.model.m[s];
   const int D = args.D;
@@ -79,112 +104,203 @@ __global__ void __launch_bounds__(64 * kRwWaves) k_mlp_rows(MlpArgs args) {
   const float* Grow = args.G + (int64_t)(arow < 0 ? 0 : arow) * D;
   const float* W1 = M.W[0];
   const float* W2 = M.W[1];
+  constexpr int NT = 64 * W;
 
-  // ---- P1: z1 = G W1^T ----
-  // Each chunk W1[0:H1][k0:k0+KC] is staged as [n][k] (zero past D; D is a
-  // multiple of 4); the next chunk and its G fragments are requested into
-  // registers before this chunk's products, so their loads overlap them.
-  constexpr int NT = 64 * kRwWaves;
-  constexpr int NS1 = H1 * KC / 4 / NT;
-  static_assert(H1 * KC / 4 % NT == 0, "whole float4 per thread");
-  float4 wpre[NS1], apre[KC / 16];
-  auto fetch1 = [&](int k0) {
+  // A staged unit is 8 k of one n.  Rows of KC k (P1-P3) hold 4 units, unit u
+  // of row n at place u ^ (n / 2 & 3); rows of H1 k (P4) H1 / 8, at
+  // u ^ (n & 7): eight lanes on consecutive rows then cover all the banks, in
+  // the stores and in the reads, without padding.
+  auto at1 = [&](int n, int u) { return 4 * n + (u ^ (n >> 1 & 3)); };
+  auto at4 = [&](int n, int u) { return H1 / 8 * n + (u ^ (n & 7)); };
+  auto stage = [&](int at, const float (&x)[8]) {
+    Split3 p;
+    split3(x, p.h, p.m, p.l);
+    wst[at] = p.h;
+    wst[WSU + at] = p.m;
+    wst[2 * WSU + at] = p.l;
+  };
+  // acc[u] += a b_u for the NU column tiles from unit place at(u)
+  auto mma = [&](auto NU, floatx4* acc, const Split3& a, auto&& at) {
+    constexpr int G = decltype(NU)::value % 2 == 0 ? 2 : 1;  // independent chains in flight
 #pragma unroll
-    for (int q = 0; q < NS1; ++q) {
-      const int x = tid + q * NT, n = x / (KC / 4), k = k0 + 4 * (x - n * (KC / 4));
-      wpre[q] = k < D ? *reinterpret_cast<const float4*>(W1 + (int64_t)n * D + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    for (int u0 = 0; u0 < decltype(NU)::value; u0 += G) {
+      Split3 b[G];
 #pragma unroll
-    for (int kb = 0; kb < KC / 16; ++kb) {
-      const int k = k0 + 16 * kb + 4 * lk;
-      apre[kb] = k < D ? *reinterpret_cast<const float4*>(Grow + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int g = 0; g < G; ++g) {
+        const int x = at(u0 + g);
+        b[g] = Split3{wst[x], wst[WSU + x], wst[2 * WSU + x]};
+      }
+      mma_split3<G>(acc + u0, a.h, a.m, a.l, b);
     }
   };
+  // The A fragment of 32 columns held as two tiles in C layout (x[t][j]: row
+  // 4 lk + j, column 16 t + lm), by way of the exchange tile: only 32 columns of
+  // a wave's rows are ever in LDS, the rest stays in registers, which leaves
+  // room for four blocks on a CU instead of two (the LDS serves a wave's
+  // accesses in order).
+  auto to_a = [&](const float (&x)[2][4]) {
+    __asm__ volatile("" ::: "memory");
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) xch[(4 * lk + j) * LDA + 16 * t2 + lm] = x[t2][j];
+    __asm__ volatile("" ::: "memory");
+    const float4 u = *reinterpret_cast<const float4*>(xch + lm * LDA + 8 * lk);
+    const float4 v = *reinterpret_cast<const float4*>(xch + lm * LDA + 8 * lk + 4);
+    const float y[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+    Split3 p;
+    split3(y, p.h, p.m, p.l);
+    return p;
+  };
+
+  // The four products walk chunks of weights: a chunk is requested into
+  // registers (w), then split and staged, and the next one (of the next
+  // product, at the end of one) requested before this one's products, so the
+  // loads overlap them.  The bases are uniform and the lanes' parts 32 bits.
+  constexpr int NU = Sh::HM * KC / 8 / NT;
+  static_assert(Sh::HM * KC / 8 % NT == 0, "whole units per thread");
+  float w[NU][8];
+  float ga[8];
+  const uint32_t uD = (uint32_t)D;
+  auto vec8 = [](const float* p, uint32_t off, float (&x)[8]) {
+    const float4 u = *reinterpret_cast<const float4*>(p + off), v = *reinterpret_cast<const float4*>(p + off + 4);
+    x[0] = u.x, x[1] = u.y, x[2] = u.z, x[3] = u.w, x[4] = v.x, x[5] = v.y, x[6] = v.z, x[7] = v.w;
+  };
+  // eight k of a row, zero past D (a multiple of 4)
+  auto tail8 = [&](const float* p, int k, float (&x)[8]) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = 0.f;
+#pragma unroll
+    for (int h = 0; h < 8; h += 4)
+      if (k + h < D) {
+        const float4 u = *reinterpret_cast<const float4*>(p + k + h);
+        x[h] = u.x, x[h + 1] = u.y, x[h + 2] = u.z, x[h + 3] = u.w;
+      }
+  };
+  // W1[n][k0 ..]
+  auto fetch1 = [&](int k0) {
+    if (k0 + KC <= D) {
+#pragma unroll
+      for (int q = 0; q < H1 * KC / 8 / NT; ++q) {
+        const uint32_t c = (uint32_t)(tid + q * NT);
+        vec8(W1 + k0, (c >> 2) * uD + 8 * (c & 3), w[q]);
+      }
+      vec8(Grow + k0, 8 * lk, ga);
+    } else {
+#pragma unroll
+      for (int q = 0; q < H1 * KC / 8 / NT; ++q) {
+        const int c = tid + q * NT;
+        tail8(W1 + (int64_t)(c >> 2) * D, k0 + 8 * (c & 3), w[q]);
+      }
+      tail8(Grow, k0 + 8 * lk, ga);
+    }
+  };
+  // W2[n][k0 ..]
+  constexpr int N2 = H2 * KC / 8;
+  auto fetch2 = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < (N2 + NT - 1) / NT; ++q) {
+      const uint32_t c = (uint32_t)(tid + q * NT);
+      if (N2 % NT == 0 || (int)c < N2) vec8(W2 + k0, (c >> 2) * H1 + 8 * (c & 3), w[q]);
+    }
+  };
+  // W2[k0 ..][n], each of the eight loads coalesced over n
+  auto fetch3 = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < H1 * KC / 8 / NT; ++q) {
+      const uint32_t c = (uint32_t)(tid + q * NT);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) w[q][k] = (W2 + (k0 + k) * H1)[8 * (c / H1) * H1 + c % H1];
+    }
+  };
+  // W1[k][c0 + n] over all k, coalesced over n
+  auto fetch4 = [&](int c0) {
+#pragma unroll
+    for (int q = 0; q < H1 * KC / 8 / NT; ++q) {
+      const uint32_t c = (uint32_t)(tid + q * NT), n = c % KC;
+      const bool in = c0 + (int)n < D;
+      const uint32_t off = in ? 8 * (c / KC) * uD + n : 0u;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float v = (W1 + (int64_t)k * D + c0)[off];
+        w[q][k] = in ? v : 0.f;
+      }
+    }
+  };
+
+  // ---- P1: z1 = G W1^T, staged as [n][k] ----
   floatx4 acc1[H1T];
 #pragma unroll
   for (int u = 0; u < H1T; ++u) acc1[u] = floatx4{0.f, 0.f, 0.f, 0.f};
   fetch1(0);
   for (int k0 = 0; k0 < D; k0 += KC) {
 #pragma unroll
-    for (int q = 0; q < NS1; ++q) {
-      const int x = tid + q * NT, n = x / (KC / 4);
-      *reinterpret_cast<float4*>(ws + n * LDW + 4 * (x - n * (KC / 4))) = wpre[q];
+    for (int q = 0; q < H1 * KC / 8 / NT; ++q) {
+      const int c = tid + q * NT;
+      stage(at1(c >> 2, c & 3), w[q]);
     }
-    float4 a[KC / 16];
-#pragma unroll
-    for (int kb = 0; kb < KC / 16; ++kb) a[kb] = apre[kb];
+    Split3 a;
+    split3(ga, a.h, a.m, a.l);
     __syncthreads();
     if (k0 + KC < D) fetch1(k0 + KC);
-#pragma unroll
-    for (int kb = 0; kb < KC / 16; ++kb)
-#pragma unroll
-      for (int u = 0; u < H1T; ++u)
-        acc1[u] = mma4_f32(acc1[u], a[kb], *reinterpret_cast<const float4*>(ws + (16 * u + lm) * LDW + 16 * kb + 4 * lk));
+    else fetch2(0);
+    mma(std::integral_constant<int, H1T>{}, acc1, a, [&](int u) { return at1(16 * u + lm, lk); });
     __syncthreads();
   }
+  // ---- P2: z2 = a1 W2^T, 32 columns of a1 = act(z1) at a time ----
   float d1[H1T][4];  // act'(z1) in C layout
-#pragma unroll
-  for (int u = 0; u < H1T; ++u) {
-    const float bias = M.b[0][16 * u + lm];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float z = acc1[u][j] + bias;
-      const float av = act_f(act1, z);
-      d1[u][j] = act_d(act1, z, av);
-      abuf[(4 * lk + j) * LDA + 16 * u + lm] = av;
-      if (args.st_a1) {
-        const int r = rows[16 * wv + 4 * lk + j];
-        if (r >= 0) args.st_a1[(int64_t)r * H1 + 16 * u + lm] = av;
-      }
-    }
-  }
-  rw_wave_sync();
-
-  // ---- P2: z2 = a1 W2^T ----
   floatx4 acc2[H2T];
 #pragma unroll
   for (int u = 0; u < H2T; ++u) acc2[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < H1; k0 += KC) {
-    for (int x = tid; x < H2 * KC / 4; x += 64 * kRwWaves) {
-      const int n = x / (KC / 4), k4 = x - n * (KC / 4);
-      const int k = k0 + 4 * k4;
-      const float4 v = k < H1 ? *reinterpret_cast<const float4*>(W2 + (int64_t)n * H1 + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-      *reinterpret_cast<float4*>(ws + n * LDW + 4 * k4) = v;
+#pragma unroll
+  for (int kc = 0; kc < H1 / KC; ++kc) {
+#pragma unroll
+    for (int q = 0; q < (N2 + NT - 1) / NT; ++q) {
+      const int c = tid + q * NT;
+      if (N2 % NT == 0 || c < N2) stage(at1(c >> 2, c & 3), w[q]);
     }
+    float a1[2][4];
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2) {
+      const int u = 2 * kc + t2;
+      act4(act1, acc1[u], M.b[0][16 * u + lm], a1[t2], d1[u]);
+      if (args.st_a1)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = rows[16 * wv + 4 * lk + j];
+          if (r >= 0) args.st_a1[(int64_t)r * H1 + 16 * u + lm] = a1[t2][j];
+        }
+    }
+    const Split3 a = to_a(a1);
     __syncthreads();
-#pragma unroll
-    for (int kb = 0; kb < KC / 16; ++kb) {
-      if (k0 + 16 * kb >= H1) break;
-      const float4 a = *reinterpret_cast<const float4*>(abuf + lm * LDA + k0 + 16 * kb + 4 * lk);
-#pragma unroll
-      for (int u = 0; u < H2T; ++u)
-        acc2[u] = mma4_f32(acc2[u], a, *reinterpret_cast<const float4*>(ws + (16 * u + lm) * LDW + 16 * kb + 4 * lk));
-    }
+    if (kc + 1 < H1 / KC) fetch2((kc + 1) * KC);
+    else fetch3(0);
+    mma(std::integral_constant<int, H2T>{}, acc2, a, [&](int u) { return at1(16 * u + lm, lk); });
     __syncthreads();
   }
-  // ---- output E = w3 . a2 + b3 and delta2 = w3 act'(z2) (over a1 in abuf) ----
-  // (every wave's reads of a1 ended before the last barrier of P2)
+  // ---- output E = w3 . a2 + b3 and delta2 = w3 act'(z2) ----
   const float* w3 = M.W[2];
   float e[4] = {0.f, 0.f, 0.f, 0.f};
+  float d2[H2T][4];
 #pragma unroll
   for (int u = 0; u < H2T; ++u) {
-    const float bias = M.b[1][16 * u + lm];
-    const float w = w3[16 * u + lm];
+    const float wu = w3[16 * u + lm];
+    float av[4];
+    act4(act2, acc2[u], M.b[1][16 * u + lm], av, d2[u]);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float z = acc2[u][j] + bias;
-      const float av = act_f(act2, z);
-      e[j] = fmaf(av, w, e[j]);
-      const float dl2 = w * act_d(act2, z, av);
-      abuf[(4 * lk + j) * LDA + 16 * u + lm] = dl2;
-      if (args.st_a2) {
+      e[j] = fmaf(av[j], wu, e[j]);
+      d2[u][j] *= wu;
+    }
+    if (args.st_a2)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
         const int r = rows[16 * wv + 4 * lk + j];
         if (r >= 0) {
-          args.st_a2[(int64_t)r * H2 + 16 * u + lm] = av;
-          args.st_d2[(int64_t)r * H2 + 16 * u + lm] = dl2;
+          args.st_a2[(int64_t)r * H2 + 16 * u + lm] = av[j];
+          args.st_d2[(int64_t)r * H2 + 16 * u + lm] = d2[u][j];
         }
       }
-    }
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -202,93 +318,72 @@ __global__ void __launch_bounds__(64 * kRwWaves) k_mlp_rows(MlpArgs args) {
       if (r >= 0) args.E_atom[r] = e[j] + M.b[2][0];
     }
   if (args.lambda == nullptr && args.st_d1 == nullptr) return;  // the same for the whole block
-  rw_wave_sync();
 
-  // ---- P3: g1 = delta2 W2, delta1 = g1 act'(z1) ----
+  // ---- P3: g1 = delta2 W2 ----
 #pragma unroll
   for (int u = 0; u < H1T; ++u) acc1[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < H2; k0 += KC) {
-    // stage W2[k0:k0+KC][0:H1] transposed: ws[n][k] = W2[k0 + k][n], four k
-    // per thread (each load coalesced over n) as one 16-byte LDS store: a
-    // thread per value would put lanes n and n + 16 on one bank
-    for (int x = tid; x < KC / 4 * H1; x += 64 * kRwWaves) {
-      const int kq = x / H1, n = x - kq * H1, k = k0 + 4 * kq;
-      float4 v;
-      v.x = k < H2 ? W2[(int64_t)k * H1 + n] : 0.f;
-      v.y = k + 1 < H2 ? W2[(int64_t)(k + 1) * H1 + n] : 0.f;
-      v.z = k + 2 < H2 ? W2[(int64_t)(k + 2) * H1 + n] : 0.f;
-      v.w = k + 3 < H2 ? W2[(int64_t)(k + 3) * H1 + n] : 0.f;
-      *reinterpret_cast<float4*>(ws + n * LDW + 4 * kq) = v;
+#pragma unroll
+  for (int kc = 0; kc < H2 / KC; ++kc) {
+#pragma unroll
+    for (int q = 0; q < H1 * KC / 8 / NT; ++q) {
+      const int c = tid + q * NT;
+      stage(at1(c % H1, c / H1), w[q]);
     }
+    const float x[2][4] = {{d2[2 * kc][0], d2[2 * kc][1], d2[2 * kc][2], d2[2 * kc][3]},
+                           {d2[2 * kc + 1][0], d2[2 * kc + 1][1], d2[2 * kc + 1][2], d2[2 * kc + 1][3]}};
+    const Split3 a = to_a(x);
     __syncthreads();
-#pragma unroll
-    for (int kb = 0; kb < KC / 16; ++kb) {
-      if (k0 + 16 * kb >= H2) break;
-      const float4 a = *reinterpret_cast<const float4*>(abuf + lm * LDA + k0 + 16 * kb + 4 * lk);
-#pragma unroll
-      for (int u = 0; u < H1T; ++u)
-        acc1[u] = mma4_f32(acc1[u], a, *reinterpret_cast<const float4*>(ws + (16 * u + lm) * LDW + 16 * kb + 4 * lk));
-    }
+    if (kc + 1 < H2 / KC) fetch3((kc + 1) * KC);
+    else fetch4(0);
+    mma(std::integral_constant<int, H1T>{}, acc1, a, [&](int u) { return at1(16 * u + lm, lk); });
     __syncthreads();
   }
-  rw_wave_sync();  // every lane's delta2 reads are done before delta1 overwrites them
+  // ---- P4: lambda = delta1 W1, delta1 = g1 act'(z1), column chunks of KC ----
+  Split3 a4[H1 / 32];  // this wave's delta1 rows as A fragments (k over H1)
 #pragma unroll
-  for (int u = 0; u < H1T; ++u)
+  for (int kb = 0; kb < H1 / 32; ++kb) {
+    float x[2][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float dd = acc1[u][j] * d1[u][j];
-      abuf[(4 * lk + j) * LDA + 16 * u + lm] = dd;
-      if (args.st_d1) {
-        const int r = rows[16 * wv + 4 * lk + j];
-        if (r >= 0) args.st_d1[(int64_t)r * H1 + 16 * u + lm] = dd;
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int u = 2 * kb + t2;
+        x[t2][j] = acc1[u][j] * d1[u][j];
+        if (args.st_d1) {
+          const int r = rows[16 * wv + 4 * lk + j];
+          if (r >= 0) args.st_d1[(int64_t)r * H1 + 16 * u + lm] = x[t2][j];
+        }
       }
-    }
+    a4[kb] = to_a(x);
+  }
   if (args.lambda == nullptr) return;
-  rw_wave_sync();
-
-  // ---- P4: lambda = delta1 W1, column chunks of KC ----
-  float4 a4[H1T];  // this wave's delta1 rows as A fragments (k over H1)
+  float* out[4];  // null for rows past the block's atoms
 #pragma unroll
-  for (int kb = 0; kb < H1T; ++kb) a4[kb] = *reinterpret_cast<const float4*>(abuf + lm * LDA + 16 * kb + 4 * lk);
-  int orow[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) orow[j] = rows[16 * wv + 4 * lk + j];
-  // each chunk W1[0:H1][c0:c0+KC] staged transposed, ws[n][k] = W1[k][c0 + n],
-  // four k per thread as one 16-byte LDS store (as in P3), the next chunk
-  // requested before this one's products
-  constexpr int NS4 = H1 * KC / (4 * NT);
-  static_assert(H1 * KC % (4 * NT) == 0, "whole groups of four values per thread");
-  float4 wp4[NS4];
-  auto fetch4 = [&](int c0) {
-#pragma unroll
-    for (int q = 0; q < NS4; ++q) {
-      const int x = tid + q * NT, kq = x / KC, n = x - kq * KC;
-      const bool in = c0 + n < D;
-      const float* w = W1 + (int64_t)(4 * kq) * D + c0 + n;
-      wp4[q] = in ? make_float4(w[0], w[D], w[2 * D], w[3 * D]) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  fetch4(0);
+  for (int j = 0; j < 4; ++j) {
+    const int r = rows[16 * wv + 4 * lk + j];
+    out[j] = r < 0 ? nullptr : args.lambda + (int64_t)r * D + lm;
+  }
   for (int c0 = 0; c0 < D; c0 += KC) {
 #pragma unroll
-    for (int q = 0; q < NS4; ++q) {
-      const int x = tid + q * NT, kq = x / KC;
-      *reinterpret_cast<float4*>(ws + (x - kq * KC) * LDT + 4 * kq) = wp4[q];
+    for (int q = 0; q < H1 * KC / 8 / NT; ++q) {
+      const int c = tid + q * NT;
+      stage(at4(c % KC, c / KC), w[q]);
     }
     __syncthreads();
     if (c0 + KC < D) fetch4(c0 + KC);
+    floatx4 acc[KC / 16];
+#pragma unroll
+    for (int ct = 0; ct < KC / 16; ++ct) acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < H1 / 32; ++kb)
+      mma(std::integral_constant<int, KC / 16>{}, acc, a4[kb], [&](int ct) { return at4(16 * ct + lm, 4 * kb + lk); });
 #pragma unroll
     for (int ct = 0; ct < KC / 16; ++ct) {
-      if (c0 + 16 * ct >= D) break;
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kb = 0; kb < H1T; ++kb)
-        acc = mma4_f32(acc, a4[kb], *reinterpret_cast<const float4*>(ws + (16 * ct + lm) * LDT + 16 * kb + 4 * lk));
-      const int col = c0 + 16 * ct + lm;
-      if (col < D)
+      const int col = c0 + 16 * ct;
+      if (col + lm < D)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (orow[j] >= 0) args.lambda[(int64_t)orow[j] * D + col] = acc[j];
+          if (out[j]) out[j][col] = acc[ct][j];
     }
     __syncthreads();
   }
@@ -621,33 +716,36 @@ void launch_mlp_rows_bf(const MlpArgs& a, int h1, int h2, int mode, int64_t N, h
 }
 
 bool mlp_rows_supported(int h1, int h2, int D) {
-  return ((h1 == 64 && h2 == 32) || (h1 == 128 && h2 == 128)) && D % 4 == 0;
+  return ((h1 == 64 && h2 == 32) || (h1 == 128 && h2 == 128) || (h1 == 256 && h2 == 128)) && D % 4 == 0;
 }
 
-// Below this many atoms a block takes 16 of them instead of 64, its four
-// waves sharing the columns of each product (the tile kernel): 64-atom blocks
+// Below this many atoms a block takes 16 of them instead of 64 or 128, its
+// waves sharing the columns of each product (the tile kernel): the larger blocks
 // would leave most CUs without one, and a block's time is then its own chain
-// of weight loads.  MLP time in us, 64 against 16 atoms a block:
-//   64-32, D 384, 4 species    192 atoms  31 / 18    8516  37 / 36   17310  47 / 54
-//   128-128, D 96, 1 species  4096 atoms  37 / 17   12288  45 / 40   16384  44 / 43
-//   128-128, D 768, 4 species 4096 atoms 107 / 43   12288 109 / 112  16384 108 / 134
-//   64-32, D 152, 1 species    256 atoms  19 / 13   12288  22 / 20   16384  22 / 29
+// of chunks.  MLP time in us, row blocks against the tile kernel:
+//   64-32, D 384, 4 species    4227 atoms  33 / 28    8516  35 / 37   17310  40 / 54
+//   64-32, D 152, 1 species    8192 atoms  20 / 17   12288  21 / 20   16384  21 / 28
+//   128-128, D 96, 1 species   8192 atoms  35 / 25   12288  37 / 39   16384  36 / 44
+//   128-128, D 768, 4 species  8192 atoms 104 / 73   12288 103 / 108  16384 104 / 135
+//   256-128, D 152, 1 species  8192 atoms  55 / 52   12288  64 / 75   16384  68 / 97
 constexpr int64_t kRowsMin = 12288;
+
+template <int A, int B, int W>
+static void launch_rows(const MlpArgs& a, int64_t N, hipStream_t s) {
+  const unsigned grid = (unsigned)((N + 16 * W - 1) / (16 * W) + a.model.S);
+  constexpr size_t lds = RowsShape<A, B, W>::lds;
+  hipLaunchKernelGGL((k_mlp_rows<A, B, W>), dim3(grid), dim3(64 * W), lds, s, a);
+}
 
 void launch_mlp_rows(const MlpArgs& a, int h1, int h2, int64_t N, hipStream_t s) {
   if (N == 0) return;
   if (N < kRowsMin) {
-    launch_mlp(a, h1, h2, 0, N, 4, s);
+    launch_mlp(a, h1, h2, 0, N, h1 == 256 ? 8 : 4, s);
     return;
   }
-  const unsigned grid = (unsigned)((N + kRwAtoms - 1) / kRwAtoms + a.model.S);
-  if (h1 == 64 && h2 == 32) {
-    constexpr size_t lds = RowsShape<4, 2>::lds;
-    hipLaunchKernelGGL((k_mlp_rows<4, 2>), dim3(grid), dim3(64 * kRwWaves), lds, s, a);
-  } else if (h1 == 128 && h2 == 128) {
-    constexpr size_t lds = RowsShape<8, 8>::lds;
-    hipLaunchKernelGGL((k_mlp_rows<8, 8>), dim3(grid), dim3(64 * kRwWaves), lds, s, a);
-  }
+  if (h1 == 64 && h2 == 32) launch_rows<4, 2, 4>(a, N, s);
+  else if (h1 == 128 && h2 == 128) launch_rows<8, 8, 8>(a, N, s);
+  else if (h1 == 256 && h2 == 128) launch_rows<16, 8, 4>(a, N, s);
 }
 
 }  // namespace nnp
