@@ -98,25 +98,38 @@ def valid_neighbor_counts(pot, rc):
     return np.bincount(rows[valid], minlength=len(off) - 1)
 
 
-SOURCES = {"k_desc": "descriptors.hip", "k_jac": "descriptors.hip", "k_mlp_rows_bf": "mlp_rows.hip", "k_mlp_rows": "mlp_rows.hip", "k_mlp": "mlp.hip", "k_force_gather": "descriptors.hip",
+SOURCES = {"k_fwd_tiles": "desc_tiles.hip", "k_adj_tiles": "desc_tiles.hip", "k_desc": "descriptors.hip", "k_jac": "descriptors.hip", "k_mlp_rows_bf": "mlp_rows.hip", "k_mlp_rows": "mlp_rows.hip", "k_mlp": "mlp.hip", "k_force_gather": "descriptors.hip",
            "k_nb": "neighbors.hip"}
+
+
+ROWS_MIN_ATOMS = 12288  # fewer atoms take the tile kernel in FP32
 
 
 def mlp_rows_plan(plan, mode, w):
     """The row-block MLP kernel the timed steps run (plan value 1 on the
-    widths and descriptor sizes it takes: k_mlp_rows in FP32, k_mlp_rows_bf
-    in the BF16 modes), else None (the tile kernel k_mlp)."""
+    widths, atom counts and descriptor sizes it takes: k_mlp_rows in FP32,
+    k_mlp_rows_bf in the BF16 modes), else None (the tile kernel k_mlp)."""
     if plan is None or plan[2] != 1:
         return None
     widths = w.model[0][0]
-    if len(widths) != 4 or tuple(widths[1:3]) not in ((64, 32), (128, 128)):
+    shapes = ((64, 32), (128, 128), (256, 128)) if mode == "fp32" else ((64, 32), (128, 128))
+    if len(widths) != 4 or tuple(widths[1:3]) not in shapes:
         return None
     if mode == "fp32":
-        return "k_mlp_rows" if w.params.dim % 4 == 0 else None
+        return "k_mlp_rows" if w.params.dim % 4 == 0 and w.system.n_atoms >= ROWS_MIN_ATOMS else None
     return "k_mlp_rows_bf" if w.params.dim % 8 == 0 else None
 
 
-def source_hash(kernel="k_desc_adj"):
+def desc_kernels(plan, desc):
+    """The descriptor kernels (forward, adjoint) the timed steps run."""
+    def name(short, waves):
+        if plan is not None and waves == 0:
+            return f"k_desc_{short}_packed"
+        return f"k_{short}_tiles" if desc == "mbp" else f"k_desc_{short}"
+    return {"desc_fwd": name("fwd", plan[0] if plan else 1), "desc_adj": name("adj", plan[1] if plan else 1)}
+
+
+def source_hash(kernel="k_adj_tiles"):
     """Hash of the source file a kernel is built from and of the compiler
     flags (counter figures are used only while it matches)."""
     from paper_2305_11805_amd import build as nnbuild
@@ -184,7 +197,7 @@ def read_pmc_csv(path, counter):
     return out
 
 
-def ingest_counters(fetch_csv, write_csv, calib_mib, workload, kernels=("k_desc_adj", "k_desc_fwd", "k_mlp_rows")):
+def ingest_counters(fetch_csv, write_csv, calib_mib, workload, kernels=("k_adj_tiles", "k_fwd_tiles", "k_mlp_rows")):
     for k in kernels:
         ingest_kernel(fetch_csv, write_csv, calib_mib, workload, k)
 
@@ -892,7 +905,7 @@ def headline(args):
     dom_ms = stages[dom][0] / max(stages[dom][1], 1)
     if dom in ("desc_adj", "desc_fwd"):
         achieved = fm[dom] / (dom_ms / 1e3) / 1e12
-        roof = {"kernel": {"desc_adj": "k_desc_adj", "desc_fwd": "k_desc_fwd"}[dom], "bound": "alu",
+        roof = {"kernel": desc_kernels(plan, args.desc)[dom], "bound": "alu",
                 "achieved": round(achieved, 3), "peak": PEAK_FP32_VALU_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_FP32_VALU_TFLOPS, 4), "traffic": None,
                 "avg_launch_ms": round(dom_ms, 5), "algorithmic_flops_per_launch": fm[dom],
@@ -917,7 +930,7 @@ def headline(args):
     # every hot kernel against its own roof: the descriptor passes against
     # FP32 VALU and HBM, the MLP against the MFMA peak of its operand type
     kern = {}
-    for stage, name in (("desc_fwd", "k_desc_fwd"), ("desc_adj", "k_desc_adj")):
+    for stage, name in desc_kernels(plan, args.desc).items():
         if stages[stage][1]:
             ms_k = stages[stage][0] / stages[stage][1]
             e = {"avg_launch_ms": round(ms_k, 5), "tflops": round(fm[stage] / (ms_k / 1e3) / 1e12, 3),
@@ -932,10 +945,12 @@ def headline(args):
         ms_k = stages["mlp"][0] / stages["mlp"][1]
         fl = mlp_flops(w, s.n_atoms)
         peak = {"fp32": PEAK_FP32_MFMA_TFLOPS, "bf16": PEAK_BF16_MFMA_TFLOPS, "bf16x3": PEAK_BF16_MFMA_TFLOPS}[args.mode]
+        mlp_name = mlp_rows_plan(plan, args.mode, w) or "k_mlp"
+        if mlp_name == "k_mlp_rows":  # each FP32 product is six of BF16 parts
+            peak = PEAK_BF16_MFMA_TFLOPS / 6
         e = {"avg_launch_ms": round(ms_k, 5), "algorithmic_flops_per_launch": fl,
              "tflops": round(fl / (ms_k / 1e3) / 1e12, 3), "peak_mfma_tflops": peak,
              "frac_mfma": round(fl / (ms_k / 1e3) / 1e12 / peak, 4)}
-        mlp_name = mlp_rows_plan(plan, args.mode, w) or "k_mlp"
         b = hbm_bytes(mlp_name)
         if b is not None:
             e["hbm_bytes_per_launch"] = b
@@ -945,7 +960,7 @@ def headline(args):
            "neighbor_build_each_step": skin == 0.0, "skin": skin, "seed": w.seed,
            "launch_plan": None if plan is None else {
                "plan": list(plan), "waves_per_atom_fwd": plan[0], "waves_per_atom_adj": plan[1],
-               "mlp": "row blocks of 64 atoms" if mlp_rows_plan(plan, args.mode, w) else f"tiles of 16 atoms, plan {plan[2]}"}}
+               "mlp": "row blocks" if mlp_rows_plan(plan, args.mode, w) else f"tiles of 16 atoms, plan {plan[2]}"}}
     if walk:
         cfg["walk"] = {"steps_timed": args.steps, "sigma_A": w.extra["step_sigma"], "list_builds_timed": n_builds,
                        "rule": "rebuild on the device when an atom moved farther than skin/2 since the last build"}
@@ -1015,7 +1030,7 @@ def main():
     ap.add_argument("--suite-out", default="suite.jsonl")
     ap.add_argument("--stored", action="store_true",
                     help="time the stored-Jacobian mode (store and reuse steps) on --config instead of the bench line")
-    ap.add_argument("--ingest-kernels", nargs="*", default=["k_desc_adj", "k_desc_fwd", "k_mlp_rows"],
+    ap.add_argument("--ingest-kernels", nargs="*", default=["k_adj_tiles", "k_fwd_tiles", "k_mlp_rows"],
                     help="kernels whose counters --ingest-counters keeps")
     ap.add_argument("--md", action="store_true",
                     help="Langevin dynamics of 16-atom cells (the Table II shape) instead of the bench line")

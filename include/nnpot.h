@@ -311,9 +311,10 @@ nn_status nn_energy_forces_noalloc(const nn_system* sys, const nn_nlist* nl, con
  * of this workload's passes -- waves per atom of the descriptor forward and
  * adjoint passes (1, 2, 4, or 0: the packed passes, four atoms of at most
  * 32 list entries per wave, mBP term) and waves per MLP tile (4, 8, or 1:
- * the row-block MLP, 64 atoms per block with the weights staged in LDS -- in
- * FP32 below 12288 atoms 16 atoms per block -- for widths (64, 32) and (128, 128) and D a multiple of 4 in FP32, of 8 in the
- * BF16 modes) -- on
+ * the row-block MLP, 64 or 128 atoms per block with the weights staged in
+ * LDS -- in FP32 below 12288 atoms 16 atoms per block -- for widths
+ * (64, 32) and (128, 128), in FP32 also (256, 128), and D a multiple of 4 in
+ * FP32, of 8 in the BF16 modes) -- on
  * `stream`, and keeps the fastest for workloads of the same shape class
  * (atom count within a factor of two, list entries per atom, descriptor
  * sizes, MLP widths and MLP mode) in a process-wide table that
