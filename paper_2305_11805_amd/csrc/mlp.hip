@@ -13,6 +13,8 @@
 // LDS to become the next product's row operand.
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "mlp_ops.h"
 
@@ -820,24 +822,27 @@ void launch_mlp_fm(const MlpFmArgs& a, int h1, int h2, int64_t N, int waves, hip
 
 // ---------------------------------------------------------------------------
 // BF16 weight copies: hi = bf16(W), lo = bf16(W - hi), each also transposed;
-// one launch for all species and layers
+// one launch for all species and layers, a matrix per blockIdx.y.  A chain of
+// one load, one division and the stores per value bounds it: with the matrices
+// one after the other in every block eight of them (57000 values) took 7.3 us,
+// now 4.3.
 // ---------------------------------------------------------------------------
 
-__global__ void k_convert_bf16(ConvJob job) {
-  for (int m = 0; m < job.n; ++m) {
-    const int R = job.rows[m], Cc = job.cols[m];
-    const int64_t total = (int64_t)R * Cc;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-      const int r = (int)(idx / Cc), c = (int)(idx % Cc);
-      const float w = job.src[m][idx];
-      const __bf16 h = (__bf16)w;
-      const __bf16 l = (__bf16)(w - (float)h);
-      job.hi[m][idx] = h;
-      job.lo[m][idx] = l;
-      job.hiT[m][(int64_t)c * R + r] = h;
-      job.loT[m][(int64_t)c * R + r] = l;
-    }
+constexpr int kConvThreads = 256;
+
+__global__ void __launch_bounds__(kConvThreads) k_convert_bf16(ConvJob job) {
+  const int m = blockIdx.y;
+  const uint32_t R = (uint32_t)job.rows[m], Cc = (uint32_t)job.cols[m];
+  const uint32_t total = R * Cc;
+  for (uint32_t idx = blockIdx.x * kConvThreads + threadIdx.x; idx < total; idx += gridDim.x * kConvThreads) {
+    const uint32_t r = idx / Cc, c = idx - r * Cc;
+    const float w = job.src[m][idx];
+    const __bf16 h = (__bf16)w;
+    const __bf16 l = (__bf16)(w - (float)h);
+    job.hi[m][idx] = h;
+    job.lo[m][idx] = l;
+    job.hiT[m][c * R + r] = h;
+    job.loT[m][c * R + r] = l;
   }
 }
 
@@ -901,7 +906,11 @@ void launch_mlp(const MlpArgs& a, int h1, int h2, int mode, int64_t N, int waves
 }
 
 void launch_convert_bf16(const ConvJob& job, hipStream_t s) {
-  hipLaunchKernelGGL(k_convert_bf16, dim3(256), dim3(256), 0, s, job);
+  if (job.n == 0) return;
+  int64_t most = 1;  // values of the largest matrix
+  for (int m = 0; m < job.n; ++m) most = std::max(most, (int64_t)job.rows[m] * job.cols[m]);
+  const unsigned blocks = (unsigned)std::min<int64_t>((most + kConvThreads - 1) / kConvThreads, 1024);
+  hipLaunchKernelGGL(k_convert_bf16, dim3(blocks, (unsigned)job.n), dim3(kConvThreads), 0, s, job);
 }
 
 void launch_energy_reduce(const float* E_atom, const int64_t* atom_ptr, int32_t B, int64_t N, double* E_struct,
