@@ -36,13 +36,17 @@ __device__ __forceinline__ float act_d2(int code, float z, float a) {
   }
 }
 
-// act(z + bias) and its derivative for four z, one branch for all of them.
+// act(z + bias) and its derivative for four z, one branch for all of them.  With
+// PASS_NAN, ReLU of NaN is NaN too, not zero.
+template <bool PASS_NAN>
 __device__ __forceinline__ void act4(int code, const floatx4& z, float bias, float (&a)[4], float (&d)[4]) {
   auto each = [&](int c) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      a[j] = act_f(c, z[j] + bias);
-      d[j] = act_d(c, z[j] + bias, a[j]);
+      const float x = z[j] + bias;
+      a[j] = act_f(c, x);
+      if (PASS_NAN && c == NN_ACT_RELU) a[j] = x != x ? x : a[j];
+      d[j] = act_d(c, x, a[j]);
     }
   };
   switch (code) {
@@ -92,53 +96,72 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& 
   }
 }
 
-// An FP32 value as three BF16 parts, x = h + m + l: each part rounds what the
-// one before left, and 3 x 8 bits hold all 24.  An infinity counts as the
-// largest BF16 value: parts of the other operand, of either sign or zero, would
-// make a NaN of it.  NaN stays (the bounds pass it on).
+// An FP32 value as three BF16 parts, x = h + m + l (the splitting of a long
+// significand into shorter ones that error-free products use): each part rounds
+// what the one before left, and 3 x 8 bits hold all 24.  Infinities, NaN and
+// values beyond the largest BF16 one have no such parts: m or l, and with it
+// every sum they enter, is then infinite or not a number, which the caller looks
+// for.  Below about 1e-33 the low parts are subnormal and the bits beyond them
+// are lost.
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void split3(const float (&x)[8], bf16x8& h, bf16x8& m, bf16x8& l) {
+struct Split3 {
+  bf16x8 h, m, l;
+};
+__device__ __forceinline__ void split_operand(const float (&x)[8], Split3& p) {
   auto pack = [](float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
   };
   auto low = [](uint32_t p) { return __uint_as_float(p << 16); };
   auto high = [](uint32_t p) { return __uint_as_float(p & 0xffff0000u); };
-  constexpr float kTop = 0x1.fep127f;
-  auto bounded = [](float v) { return __builtin_elementwise_maximum(__builtin_elementwise_minimum(v, kTop), -kTop); };
   u32x4v vh, vm, vl;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const float x0 = bounded(x[2 * q]), x1 = bounded(x[2 * q + 1]);
+    const float x0 = x[2 * q], x1 = x[2 * q + 1];
     vh[q] = pack(x0, x1);
     const float r0 = x0 - low(vh[q]), r1 = x1 - high(vh[q]);
     vm[q] = pack(r0, r1);
     vl[q] = pack(r0 - low(vm[q]), r1 - high(vm[q]));
   }
-  h = __builtin_bit_cast(bf16x8, vh);
-  m = __builtin_bit_cast(bf16x8, vm);
-  l = __builtin_bit_cast(bf16x8, vl);
+  p.h = __builtin_bit_cast(bf16x8, vh);
+  p.m = __builtin_bit_cast(bf16x8, vm);
+  p.l = __builtin_bit_cast(bf16x8, vl);
+}
+
+// The same eight values as they are, for products by FP32 instructions.
+struct Whole {
+  float4 lo, hi;
+};
+__device__ __forceinline__ void split_operand(const float (&x)[8], Whole& p) {
+  p.lo = make_float4(x[0], x[1], x[2], x[3]);
+  p.hi = make_float4(x[4], x[5], x[6], x[7]);
 }
 
 // acc[g] += a b[g] for products of values in three parts: the six partial
 // products down to 2^-16 of the whole, the small ones first (what is left
 // out, m l + l m + l l, is below 2^-23 of a product and of either sign).
-template <int G, typename B>
-__device__ __forceinline__ void mma_split3(floatx4* acc, const bf16x8& ah, const bf16x8& am, const bf16x8& al,
-                                           const B (&b)[G]) {
+template <int G>
+__device__ __forceinline__ void mma_parts(floatx4* acc, const Split3& a, const Split3 (&b)[G]) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, b[g].h, acc[g], 0, 0, 0);
+  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l, b[g].h, acc[g], 0, 0, 0);
 #pragma unroll
-  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, b[g].l, acc[g], 0, 0, 0);
+  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b[g].l, acc[g], 0, 0, 0);
 #pragma unroll
-  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, b[g].m, acc[g], 0, 0, 0);
+  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b[g].m, acc[g], 0, 0, 0);
 #pragma unroll
-  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, b[g].h, acc[g], 0, 0, 0);
+  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b[g].h, acc[g], 0, 0, 0);
 #pragma unroll
-  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, b[g].m, acc[g], 0, 0, 0);
+  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b[g].m, acc[g], 0, 0, 0);
 #pragma unroll
-  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, b[g].h, acc[g], 0, 0, 0);
+  for (int g = 0; g < G; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b[g].h, acc[g], 0, 0, 0);
+}
+// acc[g] += a b[g] by FP32 instructions (lane (lm, lk) holds the k values
+// 8 lk + i of both operands).
+template <int G>
+__device__ __forceinline__ void mma_parts(floatx4* acc, const Whole& a, const Whole (&b)[G]) {
+#pragma unroll
+  for (int g = 0; g < G; ++g) acc[g] = mma4_f32(mma4_f32(acc[g], a.lo, b[g].lo), a.hi, b[g].hi);
 }
 
 template <int MODE>

@@ -31,7 +31,9 @@
 // equal and overlapping only between waves (128-128, D 768, 32768 atoms 158 ->
 // 113 us; D 288, 262144 atoms 530 -> 297; 256-128, D 152, 16384 atoms, by
 // the tile kernel before, 97 -> 66).  Two chunks in flight instead of one, and
-// 32 atoms a wave instead of 16, were slower.
+// 32 atoms a wave instead of 16, were slower.  At 128 registers the 128-128 shape
+// writes 24 bytes a lane to scratch and reads them once a block, outside the
+// loops over chunks.
 #include <math.h>
 
 #include <type_traits>
@@ -64,38 +66,29 @@ struct RowsShape {
   static constexpr size_t lds = 3 * 16 * (size_t)WSU + sizeof(float) * (size_t)W * 16 * LDA;
 };
 
-struct Split3 {
-  bf16x8 h, m, l;
-};
-
-template <int H1T, int H2T, int W>
-__global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp_rows(MlpArgs args) {
+// One block's atoms through the network, products by `Part`: Split3, three BF16
+// parts an operand, or Whole, FP32 instructions.  Returns whether a sum of this
+// lane was not finite.
+template <int H1T, int H2T, int W, typename Part>
+__device__ __forceinline__ bool rows_block(const MlpArgs& args, int s, const int32_t* rows, float4* lds4) {
   using Sh = RowsShape<H1T, H2T, W>;
-  constexpr int NA = 16 * W;  // atoms of a block
   constexpr int H1 = Sh::H1, H2 = Sh::H2, KC = Sh::KC, LDA = Sh::LDA, WSU = Sh::WSU;
-  extern __shared__ float4 rw_lds4[];
-  bf16x8* wst = reinterpret_cast<bf16x8*>(rw_lds4);  // parts h, m, l of WSU units each
-  __shared__ int32_t rows[NA];
+  constexpr bool kSplit = std::is_same<Part, Split3>::value;
+  bf16x8* wst = reinterpret_cast<bf16x8*>(lds4);  // Split3: parts h, m, l of WSU units each
+  float4* wsf = lds4;                             // Whole: lo, hi of WSU units each
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   float* xch = reinterpret_cast<float*>(wst + 3 * WSU) + wv * 16 * LDA;  // this wave's exchange tile
   const int lm = lane & 15, lk = lane >> 4;
-  // which species / block of NA atoms
-  const int S = args.model.S;
-  int64_t t = blockIdx.x;
-  int s = 0;
-  int64_t ns = 0;
-  for (; s < S; ++s) {
-    ns = args.sp_start[s + 1] - args.sp_start[s];
-    const int64_t nt = (ns + NA - 1) / NA;
-    if (t < nt) break;
-    t -= nt;
-  }
-  if (s >= S) return;
-  const int64_t r0 = args.sp_start[s] + t * NA;
-  const int nrows = (int)min<int64_t>(NA, args.sp_start[s] + ns - r0);
-  if (tid < NA) rows[tid] = tid < nrows ? args.perm[r0 + tid] : -1;
-  __syncthreads();
+  // An operand without parts makes NaN of every sum it enters.  From G, W1 and W2
+  // that reaches the row's energy (act4 passes NaN on), from delta2 every column
+  // of g1, from delta1 every column of lambda: these are looked at.
+  bool nan = false;
+  auto look = [&](const floatx4& v) {
+    if constexpr (kSplit)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) nan = nan || v[j] != v[j];
+  };
   const MlpDev& M = args.model.m[s];
   const int D = args.D;
   const int act1 = M.act[0], act2 = M.act[1];
@@ -113,24 +106,30 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
   auto at1 = [&](int n, int u) { return 4 * n + (u ^ (n >> 1 & 3)); };
   auto at4 = [&](int n, int u) { return H1 / 8 * n + (u ^ (n & 7)); };
   auto stage = [&](int at, const float (&x)[8]) {
-    Split3 p;
-    split3(x, p.h, p.m, p.l);
-    wst[at] = p.h;
-    wst[WSU + at] = p.m;
-    wst[2 * WSU + at] = p.l;
+    Part p;
+    split_operand(x, p);
+    if constexpr (kSplit) {
+      wst[at] = p.h;
+      wst[WSU + at] = p.m;
+      wst[2 * WSU + at] = p.l;
+    } else {
+      wsf[at] = p.lo;
+      wsf[WSU + at] = p.hi;
+    }
   };
   // acc[u] += a b_u for the NU column tiles from unit place at(u)
-  auto mma = [&](auto NU, floatx4* acc, const Split3& a, auto&& at) {
-    constexpr int G = decltype(NU)::value % 2 == 0 ? 2 : 1;  // independent chains in flight
+  auto mma = [&](auto NU, floatx4* acc, const Part& a, auto&& at) {
+    constexpr int G = kSplit && decltype(NU)::value % 2 == 0 ? 2 : 1;  // independent chains in flight
 #pragma unroll
     for (int u0 = 0; u0 < decltype(NU)::value; u0 += G) {
-      Split3 b[G];
+      Part b[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const int x = at(u0 + g);
-        b[g] = Split3{wst[x], wst[WSU + x], wst[2 * WSU + x]};
+        if constexpr (kSplit) b[g] = Part{wst[x], wst[WSU + x], wst[2 * WSU + x]};
+        else b[g] = Part{wsf[x], wsf[WSU + x]};
       }
-      mma_split3<G>(acc + u0, a.h, a.m, a.l, b);
+      mma_parts<G>(acc + u0, a, b);
     }
   };
   // The A fragment of 32 columns held as two tiles in C layout (x[t][j]: row
@@ -148,8 +147,8 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
     const float4 u = *reinterpret_cast<const float4*>(xch + lm * LDA + 8 * lk);
     const float4 v = *reinterpret_cast<const float4*>(xch + lm * LDA + 8 * lk + 4);
     const float y[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-    Split3 p;
-    split3(y, p.h, p.m, p.l);
+    Part p;
+    split_operand(y, p);
     return p;
   };
 
@@ -239,8 +238,8 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
       const int c = tid + q * NT;
       stage(at1(c >> 2, c & 3), w[q]);
     }
-    Split3 a;
-    split3(ga, a.h, a.m, a.l);
+    Part a;
+    split_operand(ga, a);
     __syncthreads();
     if (k0 + KC < D) fetch1(k0 + KC);
     else fetch2(0);
@@ -263,7 +262,7 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2) {
       const int u = 2 * kc + t2;
-      act4(act1, acc1[u], M.b[0][16 * u + lm], a1[t2], d1[u]);
+      act4<kSplit>(act1, acc1[u], M.b[0][16 * u + lm], a1[t2], d1[u]);
       if (args.st_a1)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -271,7 +270,7 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
           if (r >= 0) args.st_a1[(int64_t)r * H1 + 16 * u + lm] = a1[t2][j];
         }
     }
-    const Split3 a = to_a(a1);
+    const Part a = to_a(a1);
     __syncthreads();
     if (kc + 1 < H1 / KC) fetch2((kc + 1) * KC);
     else fetch3(0);
@@ -286,7 +285,7 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
   for (int u = 0; u < H2T; ++u) {
     const float wu = w3[16 * u + lm];
     float av[4];
-    act4(act2, acc2[u], M.b[1][16 * u + lm], av, d2[u]);
+    act4<kSplit>(act2, acc2[u], M.b[1][16 * u + lm], av, d2[u]);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       e[j] = fmaf(av[j], wu, e[j]);
@@ -317,7 +316,8 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
       const int r = rows[16 * wv + 4 * lk + j];
       if (r >= 0) args.E_atom[r] = e[j] + M.b[2][0];
     }
-  if (args.lambda == nullptr && args.st_d1 == nullptr) return;  // the same for the whole block
+  look(floatx4{e[0], e[1], e[2], e[3]});
+  if (args.lambda == nullptr && args.st_d1 == nullptr) return nan;  // the same for the whole block
 
   // ---- P3: g1 = delta2 W2 ----
 #pragma unroll
@@ -331,7 +331,7 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
     }
     const float x[2][4] = {{d2[2 * kc][0], d2[2 * kc][1], d2[2 * kc][2], d2[2 * kc][3]},
                            {d2[2 * kc + 1][0], d2[2 * kc + 1][1], d2[2 * kc + 1][2], d2[2 * kc + 1][3]}};
-    const Split3 a = to_a(x);
+    const Part a = to_a(x);
     __syncthreads();
     if (kc + 1 < H2 / KC) fetch3((kc + 1) * KC);
     else fetch4(0);
@@ -339,24 +339,28 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
     __syncthreads();
   }
   // ---- P4: lambda = delta1 W1, delta1 = g1 act'(z1), column chunks of KC ----
-  Split3 a4[H1 / 32];  // this wave's delta1 rows as A fragments (k over H1)
+  Part a4[H1 / 32];  // this wave's delta1 rows as A fragments (k over H1)
 #pragma unroll
   for (int kb = 0; kb < H1 / 32; ++kb) {
     float x[2][4];
 #pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2)
+    for (int t2 = 0; t2 < 2; ++t2) {
+      const int u = 2 * kb + t2;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int u = 2 * kb + t2;
         x[t2][j] = acc1[u][j] * d1[u][j];
         if (args.st_d1) {
           const int r = rows[16 * wv + 4 * lk + j];
           if (r >= 0) args.st_d1[(int64_t)r * H1 + 16 * u + lm] = x[t2][j];
         }
       }
+    }
     a4[kb] = to_a(x);
   }
-  if (args.lambda == nullptr) return;
+  if (args.lambda == nullptr) {
+    look(acc1[0]);
+    return nan;
+  }
   float* out[4];  // null for rows past the block's atoms
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -377,6 +381,7 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
 #pragma unroll
     for (int kb = 0; kb < H1 / 32; ++kb)
       mma(std::integral_constant<int, KC / 16>{}, acc, a4[kb], [&](int ct) { return at4(16 * ct + lm, 4 * kb + lk); });
+    look(acc[0]);
 #pragma unroll
     for (int ct = 0; ct < KC / 16; ++ct) {
       const int col = c0 + 16 * ct;
@@ -387,6 +392,41 @@ __global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp
     }
     __syncthreads();
   }
+  return nan;
+}
+
+// Blocks whose products of parts gave a sum that is not finite (an infinite or
+// NaN operand, a value beyond the largest BF16 one, or a sum beyond FP32) take
+// their atoms a second time by FP32 instructions, so that infinities and NaN come
+// out as these give them; every product of such an operand is itself not finite,
+// so none goes unseen.
+template <int H1T, int H2T, int W>
+__global__ void __launch_bounds__(64 * W, H1T <= 4 ? 5 : H1T <= 8 ? 4 : 2) k_mlp_rows(MlpArgs args) {
+  constexpr int NA = 16 * W;  // atoms of a block
+  extern __shared__ float4 rw_lds4[];
+  __shared__ int32_t rows[NA];
+  __shared__ int again;
+  const int tid = threadIdx.x;
+  // which species / block of NA atoms
+  const int S = args.model.S;
+  int64_t t = blockIdx.x;
+  int s = 0;
+  int64_t ns = 0;
+  for (; s < S; ++s) {
+    ns = args.sp_start[s + 1] - args.sp_start[s];
+    const int64_t nt = (ns + NA - 1) / NA;
+    if (t < nt) break;
+    t -= nt;
+  }
+  if (s >= S) return;
+  const int64_t r0 = args.sp_start[s] + t * NA;
+  const int nrows = (int)min<int64_t>(NA, args.sp_start[s] + ns - r0);
+  if (tid < NA) rows[tid] = tid < nrows ? args.perm[r0 + tid] : -1;
+  if (tid == 0) again = 0;
+  __syncthreads();
+  if (__any(rows_block<H1T, H2T, W, Split3>(args, s, rows, rw_lds4)) && (tid & 63) == 0) again = 1;
+  __syncthreads();
+  if (again) (void)rows_block<H1T, H2T, W, Whole>(args, s, rows, rw_lds4);
 }
 
 // ---------------------------------------------------------------------------
