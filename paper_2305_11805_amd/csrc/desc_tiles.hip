@@ -168,6 +168,7 @@ struct TileRow {
   int seg[NN_MAX_SPECIES + 1];
   int n;
   int bad;
+  int all;  // adjoint: no term is left out
 };
 
 // Stages the neighbors of atom i inside rc, sorted by (species and) distance
@@ -287,6 +288,7 @@ __device__ __forceinline__ void stage_sorted(TileRow& tr, uint32_t* keys, int64_
     if (lane == 0) {
       tr.n = n;
       tr.bad = 0;
+      tr.all = 0;
     }
     wave_lds_sync();
     int slot[kTileRounds];
@@ -334,6 +336,7 @@ __device__ __forceinline__ void stage_sorted(TileRow& tr, uint32_t* keys, int64_
     if (lane == 0) {
       tr.n = n;
       tr.bad = n > kMaxNb;
+      tr.all = 0;
       if (BY_SPECIES) {
         int total = 0;
         for (int s = 0; s < S; ++s) {
@@ -827,7 +830,11 @@ __device__ __forceinline__ void adj_tiles_atom(int64_t i, const nn_system& sys, 
   const int S = P.S;
   const int n = tr.n, nblk = (n + 7) >> 3;
   const int ang0 = P.n_rad * S;
+  // An infinite or NaN lambda reaches every neighbor through its term, however
+  // small: with one, no term is left out.
+  float watch = 0.f;  // NaN once such a lambda was seen
   auto put_lam = [&](int d, float x) {
+    watch = fmaf(x, 0.f, watch);
     if (d < ang0) {
       lam_r[d] = x;
     } else {
@@ -847,7 +854,9 @@ __device__ __forceinline__ void adj_tiles_atom(int64_t i, const nn_system& sys, 
     nd[n + tid] = make_float4(0.f, 0.f, 0.f, kFar);
     nf[n + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  if (__any(watch != 0.f) && lane == 0) tr.all = 1;
   __syncthreads();
+  const bool all = __builtin_amdgcn_readfirstlane(tr.all) != 0;
   // radial: eight neighbors at a time (wave w: octets w, w + WPA, ...),
   // eight lanes each with every eighth bin; dE/dd = (dE/dr) d/r.  The other
   // waves' octets start from zero.
@@ -864,7 +873,7 @@ __device__ __forceinline__ void adj_tiles_atom(int64_t i, const nn_system& sys, 
         const int k = k0 + col;
         const float2 rs = rsg[k];
         const float d0 = r - rs.x;
-        if (__any(fabsf(d0) < kScreen)) {
+        if (all || __any(fabsf(d0) < kScreen)) {
           const float dr = d0 + (r_lo - rs.y);
           const float gk = (in && k < P.n_rad) ? lr[k] * fexp2(-dr * dr) : 0.f;
           gr = fmaf(gk, fmaf(P.drr * dr, fu.x, fu.y), gr);
@@ -882,7 +891,10 @@ __device__ __forceinline__ void adj_tiles_atom(int64_t i, const nn_system& sys, 
   const float zf = (float)P.zeta;
   const float rsv = lane < NRA ? P.rs_ang_sc[lane < NRA ? lane : 0] : -kFar;  // lane q: centre of radius term q
   // the radius terms within kScreen of [lo, hi]: one bit each
-  auto in_reach = [&](float lo, float hi) { return (uint32_t)__ballot(hi > rsv - kReach && lo < rsv + kReach); };
+  const uint32_t every = all ? (1u << NRA) - 1 : 0u;
+  auto in_reach = [&](float lo, float hi) {
+    return (uint32_t)__ballot(hi > rsv - kReach && lo < rsv + kReach) | every;
+  };
   // one triplet: the coefficients of its gradients g_j = cu v + au u and
   // g_k = cv u + av v (u, v the unit vectors)
   auto triplet = [&](const float4& u, const float4& fu, const float4& v, const float4& fv, float rb, uint32_t terms,

@@ -1,0 +1,45 @@
+"""Forces that are not finite from the distance-sorted tile passes, which leave
+out the radius terms that no neighbor feels: they are where the packed passes,
+which evaluate every term, put them."""
+import os
+
+import numpy as np
+import pytest
+
+from paper_2305_11805_amd import nnpot, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def run(pot, plan):
+    os.environ["NNPOT_PLAN"] = plan
+    try:
+        return [t.cpu().numpy().copy() for t in pot.energy_forces()[1:]]
+    finally:
+        os.environ.pop("NNPOT_PLAN", None)
+
+
+@pytest.mark.parametrize("wpa", [1, 2, 4])
+@pytest.mark.parametrize("S", [1, 2])
+@pytest.mark.parametrize("bin_", ["radial", "angular"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_non_finite_weight(value, bin_, S, wpa):
+    """A first-layer weight that is not finite makes dE/dG of its bin so for
+    every atom, and the forces of all its neighbors, near the bin or not."""
+    rng = np.random.Generator(np.random.PCG64(610))
+    s = synth.clusters_system(rng, [12] * 40, lambda n: (n / 0.05) ** (1 / 3), 0.9, S)
+    p = synth.mbp_params(S, 4.6, 16, 8, 4, eta_rad=16.0, eta_ang=12.0)
+    model = synth.random_model(S, p.dim, [64, 32], 98, act="linear", in_scale=3.0)
+    # the bin of the smallest radius: far from most neighbors
+    model[0][2][0][3, 0 if bin_ == "radial" else S * p.n_rad] = value
+    pot = nnpot.Potential(s, p, model)
+    pot.build_neighbors()
+    ref = run(pot, "0,0,4")[1]
+    got = run(pot, f"0,{wpa},4")[1]
+    nnpot.nn_check(pot.nl)
+    bad = ~np.isfinite(ref)
+    print(f"[tiles nonfinite] {bin_} S {S} {wpa} waves: {int(bad.sum())} of {bad.size} not finite", flush=True)
+    assert bad.any()
+    assert np.array_equal(~np.isfinite(got), bad)
+    if not bad.all():
+        assert np.abs(got[~bad] - ref[~bad]).max() <= 1e-4 * max(np.abs(ref[~bad]).max(), 1e-30)
