@@ -857,6 +857,17 @@ __device__ __forceinline__ void adj_tiles_atom(int64_t i, const nn_system& sys, 
   if (__any(watch != 0.f) && lane == 0) tr.all = 1;
   __syncthreads();
   const bool all = __builtin_amdgcn_readfirstlane(tr.all) != 0;
+  // without smoothing the sine has no derivative where two neighbors lie on a
+  // line with the atom: 1/r of both becomes NaN, and with it their gradients
+  if (P.eps_ang == 0.f) {
+    for (int t = tid; t < n * n; t += 64 * WPA) {
+      const int j = t / n, k = t % n;
+      const float4 u = nd[j], v = nd[k];
+      const float cx = fmaf(u.y, v.z, -u.z * v.y), cy = fmaf(u.z, v.x, -u.x * v.z), cz = fmaf(u.x, v.y, -u.y * v.x);
+      if (j != k && fmaf(cx, cx, fmaf(cy, cy, cz * cz)) == 0.f && nf[j].x * nf[k].x != 0.f) nf[j].z = __builtin_nanf("");
+    }
+    __syncthreads();
+  }
   // radial: eight neighbors at a time (wave w: octets w, w + WPA, ...),
   // eight lanes each with every eighth bin; dE/dd = (dE/dr) d/r.  The other
   // waves' octets start from zero.

@@ -43,3 +43,28 @@ def test_non_finite_weight(value, bin_, S, wpa):
     assert np.array_equal(~np.isfinite(got), bad)
     if not bad.all():
         assert np.abs(got[~bad] - ref[~bad]).max() <= 1e-4 * max(np.abs(ref[~bad]).max(), 1e-30)
+
+
+@pytest.mark.parametrize("wpa", [1, 2, 4])
+def test_lines_without_smoothing(wpa):
+    """With eps = 0 the angular term has no derivative where two neighbors and
+    the atom lie on a line: chains of 3 to 12 atoms, and the same atoms off it."""
+    rng = np.random.Generator(np.random.PCG64(611))
+    systems = []
+    for n in (3, 9, 12):
+        x = np.zeros((n, 3))
+        x[:, 0] = 1.25 * np.arange(n)
+        systems += [synth.single(x, np.zeros(n, int)), synth.single(x + rng.uniform(-0.2, 0.2, x.shape), np.zeros(n, int))]
+    s = synth.concat(systems)
+    p = synth.mbp_params(1, 4.6, 16, 8, 4, eps=0.0)
+    model = synth.random_model(1, p.dim, [64, 32], 98, in_scale=3.0)
+    pot = nnpot.Potential(s, p, model)
+    pot.build_neighbors()
+    ref, got = run(pot, "0,0,4"), run(pot, f"{wpa},{wpa},4")
+    nnpot.nn_check(pot.nl)
+    bad = ~np.isfinite(ref[1]).all(1)
+    print(f"[tiles nonfinite] lines, {wpa} waves: {int(bad.sum())} of {bad.size} atoms without a force", flush=True)
+    assert np.abs(got[0] - ref[0]).max() <= 1e-5 * np.abs(ref[0]).max()
+    assert bad.any() and not bad.all()
+    assert np.array_equal(~np.isfinite(got[1]).all(1), bad)
+    assert np.abs(got[1] - ref[1])[~bad].max() <= 1e-4 * np.abs(ref[1][~bad]).max()
