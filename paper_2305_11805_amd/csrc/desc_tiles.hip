@@ -129,7 +129,9 @@ struct PairRec {
 };
 // r = sqrt(x) and 1/r in FP64 from the hardware's reciprocal root (about 2^-23)
 // by two coupled Newton steps and a last correction of r: both within an
-// ulp, in a third of the instructions of a root and a division.
+// ulp, in a third of the instructions of a root and a division (Goldschmidt's
+// iteration).  For x = 0, atoms in one place, r = 0 and 1/r is NaN, so that the
+// radial bins stay finite and only what needs a direction does not.
 __device__ __forceinline__ void root64(double x, double& r, double& ir) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
@@ -139,7 +141,7 @@ __device__ __forceinline__ void root64(double x, double& r, double& ir) {
   e = fma(-h, g, 0.5);
   h = fma(h, e, h);
   g = fma(g, e, g);
-  r = fma(fma(-g, g, x), h, g);
+  r = x > 0.0 ? fma(fma(-g, g, x), h, g) : 0.0;
   ir = h + h;
 }
 __device__ __forceinline__ PairRec tile_record(const double (&d)[3], double r2, const DescConst& P) {

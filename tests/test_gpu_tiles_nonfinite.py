@@ -68,3 +68,25 @@ def test_lines_without_smoothing(wpa):
     assert bad.any() and not bad.all()
     assert np.array_equal(~np.isfinite(got[1]).all(1), bad)
     assert np.abs(got[1] - ref[1])[~bad].max() <= 1e-4 * np.abs(ref[1][~bad]).max()
+
+
+@pytest.mark.parametrize("wpa", [1, 2, 4])
+def test_two_atoms_in_one_place(wpa):
+    """A pair at distance zero has radial terms and no direction: energies of a
+    dimer are finite, forces and every triplet are not."""
+    a = np.array([[1.0, 2.0, 3.0]])
+    line = np.array([[0.0, 0.0, 0.0], [0.0, 0.0, 0.0], [1.5, 0.2, 0.1]])
+    s = synth.concat([synth.single(np.concatenate([a, a]), np.zeros(2, int)),
+                      synth.single(line, np.zeros(3, int)),
+                      synth.single(line * 2.0 + np.array([[0.0, 0.0, 0.0], [1.3, 0.0, 0.0], [0.0, 0.0, 0.0]]), np.zeros(3, int))])
+    p = synth.mbp_params(1, 4.6, 16, 8, 4)
+    model = synth.random_model(1, p.dim, [64, 32], 98, in_scale=3.0)
+    pot = nnpot.Potential(s, p, model)
+    pot.build_neighbors()
+    ref, got = run(pot, "0,0,4"), run(pot, f"{wpa},{wpa},4")
+    nnpot.nn_check(pot.nl)
+    assert np.isfinite(ref[0]).any() and not np.isfinite(ref[0]).all() and np.isfinite(ref[1][-3:]).all()
+    for a, b in zip(got, ref):
+        assert np.array_equal(np.isfinite(a), np.isfinite(b))
+        on = np.isfinite(b)
+        assert np.abs(a[on] - b[on]).max() <= 1e-4 * np.abs(b[on]).max()
