@@ -329,7 +329,8 @@ nn_status nn_energy_forces_noalloc(const nn_system* sys, const nn_nlist* nl, con
  * Environment:
  *   NNPOT_PLAN="f,a,m" (f, a in {0, 1, 2, 4}; m in {1, 4, 8}) overrides every
  *     plan, tuned or default, while it is set: a way to run each launch
- *     variant in tests;
+ *     variant in tests.  Its m = 1 takes the row blocks of 64 or 128 atoms
+ *     for any atom count;
  *   NN_AUTOTUNE_CACHE=<file> keeps the table in a file across processes:
  *     read on the process's first lookup, rewritten (merged) after each
  *     nn_autotune.  One JSON object per line of an array,

@@ -141,8 +141,8 @@ static PlanKey plan_key(int64_t n_atoms, int64_t capacity, const DescConst& P, c
 
 // NNPOT_PLAN="f,a,m" in the environment forces a plan on every call (waves
 // per atom of the forward and adjoint passes in {0 (packed), 1, 2, 4},
-// waves per MLP tile in {4, 8}, or 1 for the row-block MLP): lets tests run
-// each launch variant against the oracle.
+// waves per MLP tile in {4, 8}, or 1 for the row-block MLP, here for any number
+// of atoms): lets tests run each launch variant against the oracle.
 static bool forced_plan(LaunchPlan* out) {
   const char* e = getenv("NNPOT_PLAN");
   if (!e || !*e) return false;
@@ -150,7 +150,7 @@ static bool forced_plan(LaunchPlan* out) {
   if (sscanf(e, "%d,%d,%d", &f, &a, &m) != 3) return false;
   auto ok = [](int w) { return w == 0 || w == 1 || w == 2 || w == 4; };
   if (!ok(f) || !ok(a) || (m != 1 && m != 4 && m != 8)) return false;
-  *out = LaunchPlan{f, a, m};
+  *out = LaunchPlan{f, a, m, true};
   return true;
 }
 
@@ -287,14 +287,23 @@ static bool model_fused(const nn_model* m) {
   return true;
 }
 
+// Waves per tile that plan value 1 means in FP32 where the row blocks do not
+// pay (4 of 64-32 and 128-128 tiles, 8 of the wider ones).
+static int small_tile_waves(int h1) { return h1 == 256 ? 8 : 4; }
+
 // The fused two-hidden-layer MLP with this plan's launch: the row-block
 // kernel (FP32 or BF16) for plan value 1 where it takes the shape, else the
 // tile kernel.
-static void run_mlp(const MlpArgs& a, const nn_model* model, int mode, int64_t N, int waves, hipStream_t s) {
+static void run_mlp(const MlpArgs& a, const nn_model* model, int mode, int64_t N, const LaunchPlan& plan,
+                    hipStream_t s) {
   const int h1 = model->mlp[0].width[1], h2 = model->mlp[0].width[2];
+  int waves = plan.mlp_waves;
   if (waves == 1 && mode == 0 && mlp_rows_supported(h1, h2, a.D)) {
-    launch_mlp_rows(a, h1, h2, N, s);
-    return;
+    if (plan.forced || mlp_rows_pays(N)) {
+      launch_mlp_rows(a, h1, h2, N, s);
+      return;
+    }
+    waves = small_tile_waves(h1);
   }
   if (waves == 1 && mode != 0 && mlp_rows_bf_supported(h1, h2, a.D)) {
     launch_mlp_rows_bf(a, h1, h2, mode, N, s);
@@ -767,7 +776,7 @@ static void ef_enqueue(const nn_system* sys, const nn_nlist* nl, const DescConst
   a.D = P.D;
   {
     StageTimer t(NN_STAGE_MLP, s);
-    if (model_fused(model)) run_mlp(a, model, mode, N, plan.mlp_waves, s);
+    if (model_fused(model)) run_mlp(a, model, mode, N, plan, s);
     else launch_mlp_layers(lay_args(a, L), N, F != nullptr, s);
   }
   if (!F) {
@@ -1015,7 +1024,7 @@ nn_status nn_autotune(const nn_system* sys, const nn_nlist* nl, const nn_mbp_par
       bool ok = mark(0, e0);
       launch_desc_fwd(*sys, *nl, P, L.G, IdentityGroup{}, q.wpa_fwd, s);
       ok = ok && mark(0, e1) && mark(1, e0);
-      if (fused) run_mlp(a, model, mode, N, q.mlp_waves, s);
+      if (fused) run_mlp(a, model, mode, N, q, s);
       else launch_mlp_layers(lay_args(a, L), N, true, s);
       ok = ok && mark(1, e1) && mark(2, e0);
       launch_desc_adj(*sys, *nl, P, L.lam, L.pg, q.wpa_adj, s);
@@ -1204,7 +1213,7 @@ nn_status nn_energy_forces_grad(const nn_system* sys, const nn_nlist* nl, const 
       a.st_d1 = L.st_d1;
       a.st_a2 = L.st_a2;
       a.st_d2 = L.st_d2;
-      run_mlp(a, model, mode, N, plan.mlp_waves, s);
+      run_mlp(a, model, mode, N, plan, s);
     }
     WgradArgs g{};
     g.perm = L.perm;

@@ -168,6 +168,7 @@ struct IdentityGroup {
 // class.
 struct LaunchPlan {
   int wpa_fwd, wpa_adj, mlp_waves;
+  bool forced = false;  // by NNPOT_PLAN: value 1 of the MLP takes row blocks whatever the atom count
 };
 bool packed_supported(const DescConst& P);
 LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity);
@@ -264,9 +265,12 @@ void launch_species_group(const int32_t* species, int64_t N, int S, int64_t* cnt
 bool mlp_supported(int h1, int h2);
 // mode 0 FP32, 1 BF16, 2 split BF16; waves per tile 4 or 8 (0: default)
 void launch_mlp(const MlpArgs& a, int h1, int h2, int mode, int64_t N, int waves, hipStream_t s);
-// mlp_rows.hip: the FP32 row-block MLP (64 atoms per block, weights staged in
-// LDS; 16 atoms per block for few atoms); shapes (64, 32) and (128, 128) with D a multiple of 4
+// mlp_rows.hip: the FP32 row-block MLP (64 atoms per block, 128 for (128, 128);
+// weights staged in LDS); shapes (64, 32), (128, 128) and (256, 128) with D a
+// multiple of 4
 bool mlp_rows_supported(int h1, int h2, int D);
+// whether plan value 1 means it for N atoms (fewer take the tile kernel)
+bool mlp_rows_pays(int64_t N);
 void launch_mlp_rows(const MlpArgs& a, int h1, int h2, int64_t N, hipStream_t s);
 // its BF16 modes (mode 1 plain, 2 split; the BF16 weight copies prepared),
 // D a multiple of 8

@@ -759,8 +759,8 @@ bool mlp_rows_supported(int h1, int h2, int D) {
   return ((h1 == 64 && h2 == 32) || (h1 == 128 && h2 == 128) || (h1 == 256 && h2 == 128)) && D % 4 == 0;
 }
 
-// Below this many atoms a block takes 16 of them instead of 64 or 128, its
-// waves sharing the columns of each product (the tile kernel): the larger blocks
+// Below this many atoms plan value 1 means the tile kernel, whose block takes 16
+// of them, its waves sharing the columns of each product: the larger blocks
 // would leave most CUs without one, and a block's time is then its own chain
 // of chunks.  MLP time in us, row blocks against the tile kernel:
 //   64-32, D 384, 4 species    4227 atoms  33 / 28    8516  35 / 37   17310  40 / 54
@@ -769,6 +769,7 @@ bool mlp_rows_supported(int h1, int h2, int D) {
 //   128-128, D 768, 4 species  8192 atoms 104 / 73   12288 103 / 108  16384 104 / 135
 //   256-128, D 152, 1 species  8192 atoms  55 / 52   12288  64 / 75   16384  68 / 97
 constexpr int64_t kRowsMin = 12288;
+bool mlp_rows_pays(int64_t N) { return N >= kRowsMin; }
 
 template <int A, int B, int W>
 static void launch_rows(const MlpArgs& a, int64_t N, hipStream_t s) {
@@ -779,10 +780,6 @@ static void launch_rows(const MlpArgs& a, int64_t N, hipStream_t s) {
 
 void launch_mlp_rows(const MlpArgs& a, int h1, int h2, int64_t N, hipStream_t s) {
   if (N == 0) return;
-  if (N < kRowsMin) {
-    launch_mlp(a, h1, h2, 0, N, h1 == 256 ? 8 : 4, s);
-    return;
-  }
   if (h1 == 64 && h2 == 32) launch_rows<4, 2, 4>(a, N, s);
   else if (h1 == 128 && h2 == 128) launch_rows<8, 8, 8>(a, N, s);
   else if (h1 == 256 && h2 == 128) launch_rows<16, 8, 4>(a, N, s);
