@@ -42,7 +42,8 @@ static nn_status check_launch(const char* what) {
 
 // ---------------------------------------------------------------------------
 // launch plans: the defaults, or the ones nn_autotune measured for a shape
-// class (atom count within a factor of two, list entries per atom rounded
+// class (atom count within a factor of two, none on both sides of the count
+// where the FP32 MLP's kernel changes, list entries per atom rounded
 // to a multiple of four, descriptor sizes, MLP widths and mode)
 // ---------------------------------------------------------------------------
 
@@ -127,6 +128,8 @@ static PlanKey plan_key(int64_t n_atoms, int64_t capacity, const DescConst& P, c
   PlanKey k{};
   int b = 0;
   for (int64_t v = n_atoms; v > 0; v >>= 1) ++b;
+  // the class in which the row blocks begin to pay ends there
+  if (mlp_rows_pays(n_atoms) && !mlp_rows_pays((int64_t)1 << (b - 1))) ++b;
   k.n_log2 = b;
   k.row4 = n_atoms > 0 ? (int)(((capacity + n_atoms - 1) / n_atoms + 2) / 4) : 0;
   k.S = P.S;
@@ -1065,7 +1068,9 @@ nn_status nn_autotune(const nn_system* sys, const nn_nlist* nl, const nn_mbp_par
     auto desc_ok = [&](int w) { return w != 0 || pk; };
     auto mlp_ok = [&](int w) {
       if (!fused) return w == best.mlp_waves;  // no launch choice for the layer-by-layer MLP
-      if (w == 8) return h1 >= 128;
+      if (w == 8 && h1 < 128) return false;
+      // value 1 is this kernel here
+      if (w == small_tile_waves(h1) && mode == 0 && mlp_rows_supported(h1, h2, P.D) && !mlp_rows_pays(N)) return false;
       if (w == 1) return mode == 0 ? mlp_rows_supported(h1, h2, P.D) : mlp_rows_bf_supported(h1, h2, P.D);
       return true;
     };

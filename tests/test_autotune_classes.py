@@ -1,0 +1,24 @@
+"""The shape classes of tuned plans on the host: the FP32 MLP's kernel changes at
+12288 atoms, so a plan tuned on one side of it is not used on the other."""
+import json
+
+import pytest
+
+from test_autotune_cache import KEY, QUERY, built, write  # noqa: F401
+import test_autotune_cache
+
+CLASSES = [(8191, 13), (8192, 14), (12287, 14), (12288, 15), (16383, 15), (16384, 15), (32767, 15), (32768, 16)]
+
+
+@pytest.mark.parametrize("n,n_log2", CLASSES)
+def test_class_of_an_atom_count(n, n_log2, tmp_path, monkeypatch):
+    monkeypatch.setattr(test_autotune_cache, "QUERY",
+                        QUERY.replace("nn_system(192,", f"nn_system({n},").replace("nn_nlist(4000,", f"nn_nlist({20 * n},"))
+    path = str(tmp_path / "plans.json")
+    lines = []
+    for b in range(1, 20):
+        key = [b] + KEY[1:]
+        plan = [2, 4, 8] if b == n_log2 else [1, 1, 4]
+        lines.append('{"key": %s, "plan": %s}' % (json.dumps(key), json.dumps(plan)))
+    write(path, lines)
+    assert test_autotune_cache.query({"NN_AUTOTUNE_CACHE": path})["plan"] == [2, 4, 8]

@@ -80,3 +80,20 @@ def test_256_128_row_blocks_match_oracle(S, n, act):
         worst = max(worst, np.abs(g.reshape(r.shape) - r).max() / max(np.abs(r).max(), 1e-12))
     print(f"[mlp plans] 256-128 {act} S {S}: E/atom {e:.2e} F {f:.2e} gradient {worst:.2e}", flush=True)
     assert e <= E_TOL and f <= F_TOL and worst <= 1e-4
+
+
+@pytest.mark.parametrize("hidden", [[64, 32], [128, 128], [256, 128]])
+def test_tuning_below_the_row_blocks(hidden):
+    """Below 12288 atoms plan value 1 is the tile kernel's 4 waves (8 for
+    256-128): tuning does not weigh that kernel against itself, and its choice
+    holds for the whole class."""
+    rng = np.random.Generator(np.random.PCG64(621))
+    s = synth.bulk_system(rng, 701, 0.09, 1.2, [701])
+    p = synth.mbp_params(1, 4.5, 16, 8, 4)
+    pot = nnpot.Potential(s, p, synth.random_model(1, p.dim, hidden, 99, in_scale=3.0))
+    pot.build_neighbors()
+    try:
+        for _ in range(4):
+            assert pot.autotune()[2] in {64: (1,), 128: (1, 8), 256: (1, 4)}[hidden[0]]
+    finally:
+        nnpot.nn_autotune_reset()
