@@ -33,6 +33,7 @@ extern "C" {
 
 #define NN_MAX_SPECIES 8
 #define NN_MAX_LAYERS 4
+#define NN_PLAN_KERNELS 2 /* the kernels that tuned plans belong to: counted up when their relative times change */
 
 typedef enum nn_status {
   NN_OK = 0,
@@ -339,7 +340,10 @@ nn_status nn_energy_forces_noalloc(const nn_system* sys, const nn_nlist* nl, con
  *     with n_log2 the bit length of the atom count (15 from 12288 on), row4 =
  *     (ceil(capacity / atoms) + 2) / 4, h1, h2 the first two hidden widths of
  *     species 0 and mode 0 / 1 / 2 for FP32 / BF16 / split BF16.  Plans are
- *     tuned on one GPU model: keep one file per machine type.  Best effort:
+ *     tuned on one GPU model: keep one file per machine type.  A first entry
+ *     {"kernels": NN_PLAN_KERNELS} names the kernels they were tuned on; a
+ *     file of other kernels is not used and replaced.  One without that entry
+ *     is used: tune anew (into a new file) after an update.  Best effort:
  *     a file that cannot be read or written only costs speed.
  */
 nn_status nn_autotune(const nn_system* sys, const nn_nlist* nl, const nn_mbp_params* p, const nn_model* model,

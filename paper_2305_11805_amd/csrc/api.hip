@@ -63,9 +63,12 @@ static std::map<PlanKey, LaunchPlan> g_plans;
 // winning; written to a temporary file and renamed into place).  One entry
 // per line of a JSON array:
 //   {"key": [n_log2, row4, S, n_theta, n_rs_ang, n_rad, h1, h2, mode], "plan": [f, a, m]}
-// Lines that do not parse, or whose plan is out of range, are skipped.  The
-// cache is best effort: a file that cannot be read or written changes nothing
-// but the speed.
+// A first entry {"kernels": g} names the kernels its plans were measured on: a
+// file of other kernels than this library's is not used, and replaced by the
+// next nn_autotune.  One without it (written before the entry was, or by hand)
+// is used and stays without.  Lines that do not parse, or whose plan is out of
+// range, are skipped.  The cache is best effort: a file that cannot be read or
+// written changes nothing but the speed.
 static bool g_cache_loaded = false;
 
 static const char* cache_path() {
@@ -78,39 +81,50 @@ static bool plan_valid(const LaunchPlan& q) {
   return w(q.wpa_fwd) && w(q.wpa_adj) && (q.mlp_waves == 0 || q.mlp_waves == 1 || q.mlp_waves == 4 || q.mlp_waves == 8);
 }
 
-static void cache_read(const char* path, std::map<PlanKey, LaunchPlan>& into, bool overwrite) {
+// Returns whether the file holds plans that name no kernels.
+static bool cache_read(const char* path, std::map<PlanKey, LaunchPlan>& into, bool overwrite) {
   FILE* f = fopen(path, "r");
-  if (!f) return;
+  if (!f) return false;
   char line[512];
+  bool named = false, any = false;
   while (fgets(line, sizeof line, f)) {
+    int g = 0;
+    if (sscanf(line, " {\"kernels\": %d}", &g) == 1) {
+      if (g != NN_PLAN_KERNELS) break;
+      named = true;
+      continue;
+    }
     PlanKey k{};
     LaunchPlan q{};
     const int n = sscanf(line, " {\"key\": [%d, %d, %d, %d, %d, %d, %d, %d, %d], \"plan\": [%d, %d, %d]}", &k.n_log2,
                          &k.row4, &k.S, &k.nt, &k.nra, &k.n_rad, &k.h1, &k.h2, &k.mode, &q.wpa_fwd, &q.wpa_adj,
                          &q.mlp_waves);
     if (n != 12 || !plan_valid(q)) continue;
+    any = true;
     if (overwrite) into[k] = q;
     else into.emplace(k, q);
   }
   fclose(f);
+  return any && !named;
 }
 
 static void cache_load_locked() {
   if (g_cache_loaded) return;
   g_cache_loaded = true;
-  if (const char* path = cache_path()) cache_read(path, g_plans, false);
+  if (const char* path = cache_path()) (void)cache_read(path, g_plans, false);
 }
 
 static void cache_store_locked() {
   const char* path = cache_path();
   if (!path) return;
   std::map<PlanKey, LaunchPlan> all;
-  cache_read(path, all, true);  // entries other processes wrote meanwhile
+  const bool unnamed = cache_read(path, all, true);  // entries other processes wrote meanwhile
   for (const auto& kv : g_plans) all[kv.first] = kv.second;
   const std::string tmp = std::string(path) + ".tmp." + std::to_string((long)getpid());
   FILE* f = fopen(tmp.c_str(), "w");
   if (!f) return;
   bool ok = fprintf(f, "[\n") > 0;
+  if (!unnamed) ok = ok && fprintf(f, "{\"kernels\": %d}%s\n", NN_PLAN_KERNELS, all.empty() ? "" : ",") > 0;
   size_t left = all.size();
   for (const auto& kv : all) {
     const PlanKey& k = kv.first;

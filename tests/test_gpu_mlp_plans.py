@@ -2,7 +2,9 @@
 size, so that small systems can check them against the FP64 oracle (here the
 256-128 shape: energies, forces, the weight gradient, the same bits on every
 run), and the default rules blocks of 16 atoms below 12288."""
+import json
 import os
+import re
 
 import numpy as np
 import pytest
@@ -13,6 +15,7 @@ from paper_2305_11805_amd import nnpot, synth
 from helpers import E_TOL, F_TOL
 
 pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 class plan:
@@ -97,3 +100,26 @@ def test_tuning_below_the_row_blocks(hidden):
             assert pot.autotune()[2] in {64: (1,), 128: (1, 8), 256: (1, 4)}[hidden[0]]
     finally:
         nnpot.nn_autotune_reset()
+
+
+@pytest.mark.parametrize("before", ["absent", "current", "other", "unnamed"])
+def test_plan_file_names_its_kernels(before, tmp_path, monkeypatch):
+    """What nn_autotune writes: plans of other kernels go, the same kernels' and
+    those of a file that names none stay, and such a file stays without a name."""
+    own = int(re.search(r"#define NN_PLAN_KERNELS (\d+)", open(os.path.join(ROOT, "include", "nnpot.h")).read()).group(1))
+    path = tmp_path / "plans.json"
+    entry = {"key": [20, 1, 1, 8, 4, 16, 64, 32, 0], "plan": [1, 1, 4]}
+    first = {"current": [{"kernels": own}], "other": [{"kernels": own + 1}], "unnamed": []}
+    if before != "absent":
+        path.write_text("[\n" + ",\n".join(json.dumps(e) for e in first[before] + [entry]) + "\n]\n")
+    monkeypatch.setenv("NN_AUTOTUNE_CACHE", str(path))
+    s, p, model = bulk(432, 1, [64, 32])
+    nnpot.nn_autotune_reset()
+    pot = nnpot.Potential(s, p, model)
+    pot.build_neighbors()
+    pot.autotune()
+    nnpot.nn_autotune_reset()
+    out = json.loads(path.read_text())
+    assert (out[0] == {"kernels": own}) == (before != "unnamed")
+    assert (entry in out) == (before in ("current", "unnamed"))
+    assert sum("key" in e for e in out) == 1 + (before in ("current", "unnamed"))
