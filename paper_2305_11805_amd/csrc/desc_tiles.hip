@@ -461,14 +461,22 @@ struct StripTri {
 };
 
 // The descriptor row of atom i by the block (WPA waves).  MANY: three or
-// more species.
+// more species.  The waves share the triplets; two waves of 16x8 bins share the
+// angle terms instead (AS = 2): each takes all triplets with eight terms, in 96
+// registers and five waves per SIMD where 128 bins take 168 and three, and no
+// sums pass between them.  4096 atoms of 52 neighbors 69 -> 63 us, 2048 44 -> 38,
+// for the triplets' geometry formed twice (one wave at 65536 atoms: 717, two 732).
 template <int NT, int NRA, int WPA, int ZC, bool MANY>
 __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn_system& sys,
                                                const int64_t* __restrict__ offsets, const int32_t* __restrict__ nbr,
                                                const int8_t* __restrict__ shift, const DescConst& P,
                                                float* __restrict__ G, int64_t* meta) {
   constexpr int NB = NT * NRA;
-  constexpr int NS = NB > 64 ? 64 : NB;  // bins summed over the wave at a time
+  constexpr int AS = NT * NRA == 128 && WPA == 2 ? 2 : 1;
+  constexpr int TW = WPA / AS;              // waves that share the triplets
+  constexpr int NTW = NT / AS;              // angle terms of a wave
+  constexpr int NBW = NTW * NRA;            // and its bins of a species-pair block
+  constexpr int NS = NBW > 64 ? 64 : NBW;  // bins summed over the wave at a time
   __shared__ TileRow tr;
   __shared__ float4 nd[kMaxNb];  // unit vector, scaled distance (hi)
   __shared__ float4 nf[kMaxNb];  // fc, scaled distance (lo), distance scaled for the radial bins (hi, lo)
@@ -536,9 +544,17 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
       __syncthreads();
     }
   }
+  const int tw = AS > 1 ? 0 : wv, p0 = AS > 1 ? NTW * wv : 0;  // its share of the triplets, its first angle term
+  auto bin = [&](int x) { return AS > 1 ? x / NTW * NT + p0 + x % NTW : x; };  // place of the wave's bin x in the block
+  float x_a[NTW], x_b[NTW];
+#pragma unroll
+  for (int p = 0; p < NTW; ++p) {
+    x_a[p] = AS > 1 && p0 ? P.x_a[(NT - NTW) + p] : P.x_a[p];
+    x_b[p] = AS > 1 && p0 ? P.x_b[(NT - NTW) + p] : P.x_b[p];
+  }
   float* ang = Gi + n_rad * S;
   // adds the triplet of slots j and k (take: this lane holds one) to acc
-  auto triplet = [&](int j, int k, bool take, float (&acc)[NB]) {
+  auto triplet = [&](int j, int k, bool take, float (&acc)[NBW]) {
     const float4 u = nd[j], v = nd[k];
     const float4 fu = nf[j], fv = nf[k];
     // cos, the smoothed sine from the cross product, the scaled average
@@ -551,11 +567,11 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
     const float lo = ((u.w - (sum - bb)) + (v.w - bb)) + (fu.y + fv.y);
     const float rb = take ? sum : kFar;
     const float F2 = take ? 2.0f * fu.x * fv.x : 0.f;
-    if constexpr (NT <= 8) {
-      float x[NT], A[NT];
+    if constexpr (NTW <= 8) {
+      float x[NTW], A[NTW];
 #pragma unroll
-      for (int p = 0; p < NT; ++p) x[p] = fmaf(c, P.x_a[p], fmaf(ssm, P.x_b[p], P.x_c));
-      ipow_sel<(ZC > 0 ? ZC : 0), NT>(x, P.zeta, A);
+      for (int p = 0; p < NTW; ++p) x[p] = fmaf(c, x_a[p], fmaf(ssm, x_b[p], P.x_c));
+      ipow_sel<(ZC > 0 ? ZC : 0), NTW>(x, P.zeta, A);
 #pragma unroll
       for (int q = 0; q < NRA; ++q) {
         const float d0 = rb - P.rs_ang_sc[q];
@@ -563,7 +579,7 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
           const float dq = d0 + (lo - P.rs_ang_sc_lo[q]);
           const float R = fexp2(-dq * dq) * F2;
 #pragma unroll
-          for (int p = 0; p < NT; ++p) acc[q * NT + p] = fmaf(A[p], R, acc[q * NT + p]);
+          for (int p = 0; p < NTW; ++p) acc[q * NTW + p] = fmaf(A[p], R, acc[q * NTW + p]);
         }
       }
     } else {
@@ -601,7 +617,7 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
     // ones, so that the two are of like size).  With 4 species and 45
     // neighbors a block holds 66 or 128 triplets: 21 steps of the wave
     // instead of 26, and half as many sums over lanes.
-    constexpr int E = NB / 32 > 0 ? NB / 32 : 1;
+    constexpr int E = NBW / 32 > 0 ? NBW / 32 : 1;
     const int hl = lane & 31, half = lane >> 5;
     const int nblk = S * (S + 1) / 2, noff = S * (S - 1) / 2;
     for (int p0 = 0; p0 < nblk; p0 += 2) {
@@ -622,34 +638,34 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
       const int na = tr.seg[a + 1] - sa, nbb = tr.seg[b + 1] - sb;
       const int T = !has ? 0 : same ? na * (na - 1) / 2 : na * nbb;
       const int Tmax = max(__builtin_amdgcn_readlane(T, 0), __builtin_amdgcn_readlane(T, 32));
-      float acc[NB];
+      float acc[NBW];
 #pragma unroll
-      for (int x = 0; x < NB; ++x) acc[x] = 0.f;
+      for (int x = 0; x < NBW; ++x) acc[x] = 0.f;
       StripRect rect;
       StripTri tri;
-      rect.init(na, nbb, wv * 32 + hl);
-      tri.init(na, wv * 32 + hl);
-      for (int t0 = wv * 32; t0 < Tmax; t0 += 32 * WPA) {
+      rect.init(na, nbb, tw * 32 + hl);
+      tri.init(na, tw * 32 + hl);
+      for (int t0 = tw * 32; t0 < Tmax; t0 += 32 * TW) {
         const bool take = t0 + hl < T;
         int j = 0, k = 0;
         if (take) {
           if (same) {
             tri.at(j, k);
-            tri.step(32 * WPA);
+            tri.step(32 * TW);
           } else {
             rect.at(j, k);
-            rect.step(32 * WPA);
+            rect.step(32 * TW);
           }
         }
         triplet(take ? sa + j : 0, take ? sb + k : 0, take, acc);
       }
       float sums[E];
-      half_sums<NB>(acc, sums);
+      half_sums<NBW>(acc, sums);
       float* out = ang + pair_block(S, a, b) * NB;
-      if constexpr (WPA == 1) {
-        if (has && hl < NB)
+      if constexpr (TW == 1) {
+        if (has && hl < NBW)
 #pragma unroll
-          for (int e = 0; e < E; ++e) out[E * hl + e] = sums[e];
+          for (int e = 0; e < E; ++e) out[bin(E * hl + e)] = sums[e];
       } else {
         if (hl < NB)
 #pragma unroll
@@ -672,37 +688,37 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
         const int na = tr.seg[a + 1] - sa, nbb = tr.seg[b + 1] - sb;
         const bool same = a == b;
         const int T = same ? na * (na - 1) / 2 : na * nbb;
-        float acc[NB];
+        float acc[NBW];
 #pragma unroll
-        for (int x = 0; x < NB; ++x) acc[x] = 0.f;
+        for (int x = 0; x < NBW; ++x) acc[x] = 0.f;
         StripRect rect;
         StripTri tri;
-        if (same) tri.init(na, tid);
-        else rect.init(na, nbb, tid);
-        for (int t0 = wv * kWave; t0 < T; t0 += kWave * WPA) {
+        if (same) tri.init(na, tw * kWave + lane);
+        else rect.init(na, nbb, tw * kWave + lane);
+        for (int t0 = tw * kWave; t0 < T; t0 += kWave * TW) {
           const bool take = t0 + lane < T;
           int j = 0, k = 0;
           if (same) {
             if (take) tri.at(j, k);
-            tri.step(kWave * WPA);
+            tri.step(kWave * TW);
           } else {
             if (take) rect.at(j, k);
-            rect.step(kWave * WPA);
+            rect.step(kWave * TW);
           }
           triplet(sa + j, sb + k, take, acc);
         }
 #pragma unroll
-        for (int h = 0; h < NB / NS; ++h) {
+        for (int h = 0; h < NBW / NS; ++h) {
           float part[NS];
 #pragma unroll
           for (int x = 0; x < NS; ++x) part[x] = acc[h * NS + x];
           const float sum = wave_sums<NS>(part);
           if (lane < NS) {
-            if constexpr (WPA == 1) ang[h * NS + lane] = sum;
+            if constexpr (TW == 1) ang[bin(h * NS + lane)] = sum;
             else xch[wv][h * NS + lane] = sum;
           }
         }
-        if constexpr (WPA > 1) {
+        if constexpr (TW > 1) {
           __syncthreads();
           for (int x = tid; x < NB; x += 64 * WPA) {
             float v = 0.f;
@@ -717,8 +733,18 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
   }
 }
 
+// Waves per SIMD that the registers of a wave's bins leave.  At these bounds the
+// 8x8 passes keep up to 64 bytes a lane in scratch with three or more species, 20
+// with fewer and several waves, and 128 bins 12 to 84: bins and terms of the
+// inner loop stay in registers.
+constexpr int fwd_waves(int NT, int NRA, int WPA, bool MANY) {
+  const bool half = NT * NRA == 128 && WPA == 2;  // AS = 2
+  const int bins = NT * NRA / (half ? 2 : 1);
+  return bins <= 32 ? 6 : bins > 64 ? 3 : NT == 8 || (half && !MANY) ? 5 : 4;
+}
+
 template <int NT, int NRA, int WPA, int ZC, bool MANY>
-__global__ void __launch_bounds__(64 * WPA, NT * NRA <= 32 ? 6 : NT * NRA == 64 ? (NT == 8 ? 5 : 4) : 3) k_fwd_tiles(nn_system sys, const int64_t* __restrict__ offsets,
+__global__ void __launch_bounds__(64 * WPA, fwd_waves(NT, NRA, WPA, MANY)) k_fwd_tiles(nn_system sys, const int64_t* __restrict__ offsets,
                                                         const int32_t* __restrict__ nbr,
                                                         const int8_t* __restrict__ shift, DescConst P,
                                                         float* __restrict__ G, int64_t* meta, IdentityGroup one,

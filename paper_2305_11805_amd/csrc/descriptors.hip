@@ -1973,22 +1973,35 @@ bool packed_supported(const DescConst& P) {
 }
 
 // Waves per atom.  Forward: one, except that the few atoms of a small system
-// leave the chip waiting for single waves (one species, 52 neighbors: four
-// waves 20 us, two 23, one 33 at 1024 atoms; 50, 47 and 53 at 4096; 91, 79
-// and 80 at 8192); three or more species have short species-pair blocks that
-// more waves cannot share (four species: one wave 71, two 82 us at 4096
-// atoms).  Adjoint: two, which share an atom's records in LDS and so keep
-// more waves resident than one (one species: 341 against 409 us at 32768
-// atoms), four up to 8192 atoms (60 against 65 us at 4096).  The packed passes for short
-// rows (small molecules: at most 24 list entries per atom on average).  MLP:
-// the row-block kernel.
+// leave the chip waiting for single waves (8x8 bins, one species, 52 neighbors:
+// four waves 20 us, two 22, one 33 at 1024 atoms; 48, 45 and 48 at 4096; 90, 79
+// and 79 at 8192); three or more species have short species-pair blocks that
+// more waves cannot share (four species: one wave 68, two 82 us at 4096
+// atoms).  16x8 bins: two, each with half the angle terms, since one wave's 128
+// bins leave three waves per SIMD (one species, 64 to 1024 cells of 16 atoms, two
+// waves against one: 28 and 38 us at 1024 atoms, 38 and 41 at 2048, 55 and 65 at
+// 3200, 63 and 70 at 4096, 88 and 95 at 6400, 129 and 132 at 10240; above 16384
+// atoms one, 371 against 376 at 32768); four waves, sharing the triplets, up to
+// 768 atoms of at most two species (22 against 29 us).
+// Adjoint: two, which share an atom's records in LDS and so keep more waves
+// resident than one (8x8, one species: 343 against 392 us at 32768 atoms); four
+// for few atoms.  That line lies where four waves an atom fill the chip: later
+// the more registers a wave needs, earlier the less there is to share.  Four
+// against two, us: 8x8 58 and 61 at 4096 atoms, 107 and 107 at 8192 (two species
+// 190 and 204); 8x4 45 and 46 at 4096, 84 and 79 at 8192 (4x8 81 and 77, 4x4 72
+// and 66); 16x8, which holds four waves per SIMD, 40 and 44 at 1536, 47 and 44 at
+// 2048, 81 and 78 at 4096, 150 and 138 at 8192 (16x4 the same way).
+// The packed passes for short rows (small molecules: at most 24 list entries per
+// atom on average).  MLP: the row-block kernel.
 LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity) {
   const bool bp = P.kind == NN_DESC_BP;
   const int w = n_atoms <= 16384 ? 2 : 1;  // the BP term's passes
   LaunchPlan plan{w, w, 1};  // the row-block MLP where it takes the shape (FP32), else the tile kernel's default
   if (!bp) {
-    plan.wpa_fwd = n_atoms <= 1024 ? 4 : n_atoms <= (P.S >= 3 ? 2048 : 8192) ? 2 : 1;
-    plan.wpa_adj = n_atoms <= 8192 ? 4 : 2;
+    const int bins = P.n_theta * P.n_rs_ang;
+    if (bins == 128) plan.wpa_fwd = n_atoms <= 768 && P.S <= 2 ? 4 : n_atoms <= 16384 ? 2 : 1;
+    else plan.wpa_fwd = n_atoms <= 1024 ? 4 : n_atoms <= (P.S >= 3 ? 2048 : 8192) ? 2 : 1;
+    plan.wpa_adj = n_atoms <= (P.n_theta == 16 ? 1536 : bins == 64 ? 8192 : 4096) ? 4 : 2;
   }
   const bool short_rows = n_atoms > 0 && capacity <= 24 * n_atoms;
   if (short_rows && packed_supported(P)) {
@@ -2128,8 +2141,8 @@ void launch_desc_tan(const nn_system& sys, const nn_nlist& nl, const DescConst& 
   NNP_DISPATCH(A, B, (launch_tan_t<A, B>(sys, nl, P, v, U, wpa, s)));
 }
 
-// F from the per-entry gradients; blocks past the gather's sum the
-// per-structure energies (ej.B of them) in the same launch.
+// F from the per-entry gradients; the first ej.B blocks of the same launch sum
+// the per-structure energies.
 void launch_force_gather(const nn_system& sys, const nn_nlist& nl, const float4* pg, float* F, const EnergyJob& ej,
                          hipStream_t s, const float* Fc) {
   unsigned ng = (unsigned)((sys.n_atoms * 16 + 255) / 256);
