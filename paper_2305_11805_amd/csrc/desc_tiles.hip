@@ -743,8 +743,8 @@ constexpr int fwd_waves(int NT, int NRA, int WPA, bool MANY) {
   return bins <= 32 ? 6 : bins > 64 ? 3 : NT == 8 || (half && !MANY) ? 5 : 4;
 }
 
-template <int NT, int NRA, int WPA, int ZC, bool MANY>
-__global__ void __launch_bounds__(64 * WPA, fwd_waves(NT, NRA, WPA, MANY)) k_fwd_tiles(nn_system sys, const int64_t* __restrict__ offsets,
+template <int NT, int NRA, int WPA, int ZC, bool MANY, int WAVES = fwd_waves(NT, NRA, WPA, MANY)>
+__global__ void __launch_bounds__(64 * WPA, WAVES) k_fwd_tiles(nn_system sys, const int64_t* __restrict__ offsets,
                                                         const int32_t* __restrict__ nbr,
                                                         const int8_t* __restrict__ shift, DescConst P,
                                                         float* __restrict__ G, int64_t* meta, IdentityGroup one,
@@ -1216,6 +1216,17 @@ __global__ void __launch_bounds__(64) k_adj_tiles_long(nn_system sys, const int6
 template <int NT, int NRA, int WPA, int ZC, bool MANY>
 static void fwd_w(const nn_system& sys, const nn_nlist& nl, const DescConst& P, float* G, IdentityGroup one,
                   hipStream_t s) {
+  // Up to 2048 atoms two waves each are at most four for each of the 1024 SIMDs.
+  // Where a fifth fits, some get five and others three (after a list build 42 us at
+  // 2048 atoms); where only four do, each gets its share (38 us).  More atoms need
+  // the fifth: 42 against 47 us at 2064.
+  if constexpr (fwd_waves(NT, NRA, WPA, MANY) == 5 && NT == 16) {
+    if (sys.n_atoms <= 2048) {
+      hipLaunchKernelGGL((k_fwd_tiles<NT, NRA, WPA, ZC, MANY, 4>), dim3(atom_grid(sys.n_atoms, nl.order)),
+                         dim3(64 * WPA), 0, s, sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
+      return;
+    }
+  }
   hipLaunchKernelGGL((k_fwd_tiles<NT, NRA, WPA, ZC, MANY>), dim3(atom_grid(sys.n_atoms, nl.order)), dim3(64 * WPA), 0, s,
                      sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
 }
