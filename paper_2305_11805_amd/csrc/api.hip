@@ -159,7 +159,7 @@ static PlanKey plan_key(int64_t n_atoms, int64_t capacity, const DescConst& P, c
 // NNPOT_PLAN="f,a,m" in the environment forces a plan on every call (waves
 // per atom of the forward and adjoint passes in {0 (packed), 1, 2, 4},
 // waves per MLP tile in {4, 8}, or 1 for the row-block MLP, here for any number
-// of atoms): lets tests run each launch variant against the oracle.
+// of atoms; the descriptor tangent takes the forward's waves): lets tests run each launch variant against the oracle.
 static bool forced_plan(LaunchPlan* out) {
   const char* e = getenv("NNPOT_PLAN");
   if (!e || !*e) return false;
@@ -167,7 +167,7 @@ static bool forced_plan(LaunchPlan* out) {
   if (sscanf(e, "%d,%d,%d", &f, &a, &m) != 3) return false;
   auto ok = [](int w) { return w == 0 || w == 1 || w == 2 || w == 4; };
   if (!ok(f) || !ok(a) || (m != 1 && m != 4 && m != 8)) return false;
-  *out = LaunchPlan{f, a, m, true};
+  *out = LaunchPlan{f, a, m, f, true};
   return true;
 }
 
@@ -178,7 +178,13 @@ static LaunchPlan plan_for(int64_t n_atoms, int64_t capacity, const DescConst& P
   std::lock_guard<std::mutex> g(g_pmu);
   cache_load_locked();
   auto it = g_plans.find(k);
-  return it != g_plans.end() ? it->second : plan_default(n_atoms, P, capacity);
+  LaunchPlan plan = plan_default(n_atoms, P, capacity);
+  if (it != g_plans.end()) {
+    const int tan = P.kind == NN_DESC_BP ? it->second.wpa_fwd : plan.wpa_tan;
+    plan = it->second;
+    plan.wpa_tan = tan;
+  }
+  return plan;
 }
 
 // ---------------------------------------------------------------------------
@@ -954,7 +960,7 @@ nn_status nn_descriptor_tangent(const nn_system* sys, const nn_nlist* nl, const 
   if ((!v || !U) && sys->n_atoms > 0) return fail(NN_E_INVALID, "v/U is NULL");
   if (nl->radius < p->rc) return fail(NN_E_INVALID, "list radius %g < rc %g", nl->radius, p->rc);
   hipStream_t s = (hipStream_t)stream;
-  launch_desc_tan(*sys, *nl, P, v, U, plan_for(sys->n_atoms, nl->capacity, P, nullptr, 0).wpa_fwd, s);
+  launch_desc_tan(*sys, *nl, P, v, U, plan_for(sys->n_atoms, nl->capacity, P, nullptr, 0).wpa_tan, s);
   return check_launch("nn_descriptor_tangent");
 }
 
@@ -1175,7 +1181,7 @@ nn_status nn_energy_forces_grad(const nn_system* sys, const nn_nlist* nl, const 
       a.D = P.D;
       LayArgs la = lay_args(a, L);
       if (dL_dF) {
-        launch_desc_tan(*sys, *nl, P, dL_dF, L.lam, plan.wpa_fwd, s);
+        launch_desc_tan(*sys, *nl, P, dL_dF, L.lam, plan.wpa_tan, s);
         la.U = L.lam;
         launch_mlp_layers_tangent(la, N, s);
       } else {
@@ -1198,7 +1204,7 @@ nn_status nn_energy_forces_grad(const nn_system* sys, const nn_nlist* nl, const 
     if (dL_dF) {
       // descriptor tangent along dL/dF into the lambda buffer (not needed
       // here), then the MLP with its tangent in FP32
-      launch_desc_tan(*sys, *nl, P, dL_dF, L.lam, plan.wpa_fwd, s);
+      launch_desc_tan(*sys, *nl, P, dL_dF, L.lam, plan.wpa_tan, s);
       MlpFmArgs f{};
       f.model = a.model;
       f.G = L.G;

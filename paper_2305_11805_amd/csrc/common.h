@@ -168,6 +168,7 @@ struct IdentityGroup {
 // class.
 struct LaunchPlan {
   int wpa_fwd, wpa_adj, mlp_waves;
+  int wpa_tan = 0;      // the descriptor tangent's; not tuned and not in plan files
   bool forced = false;  // by NNPOT_PLAN: value 1 of the MLP takes row blocks whatever the atom count
 };
 bool packed_supported(const DescConst& P);

@@ -1991,6 +1991,12 @@ bool packed_supported(const DescConst& P) {
 // 190 and 204); 8x4 45 and 46 at 4096, 84 and 79 at 8192 (4x8 81 and 77, 4x4 72
 // and 66); 16x8, which holds four waves per SIMD, 40 and 44 at 1536, 47 and 44 at
 // 2048, 81 and 78 at 4096, 150 and 138 at 8192 (16x4 the same way).
+// Tangent (MFMA, triplets in index order; mBP), us with four, two and one wave:
+// one species 17, 25 and 39 at 16 atoms, 26, 32 and 47 at 1024, 69, 71 and 90 at
+// 4096, 250, 246 and 272 at 16384, 965, 927 and 985 at 65536; two species the same
+// up to 16384 atoms (two and one: 127 and 136 at 8192, 232 and 234 at 16384, 437
+// and 425 at 32768); three or more, whose pair blocks are short, 35 and 47 at 1024,
+// 58 and 56 at 2048, 87 and 76 at 3000.
 // The packed passes for short rows (small molecules: at most 24 list entries per
 // atom on average).  MLP: the row-block kernel.
 LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity) {
@@ -2001,16 +2007,19 @@ LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity) {
     const int bins = P.n_theta * P.n_rs_ang;
     if (bins == 128) plan.wpa_fwd = n_atoms <= 768 && P.S <= 2 ? 4 : n_atoms <= 16384 ? 2 : 1;
     else plan.wpa_fwd = n_atoms <= 1024 ? 4 : n_atoms <= (P.S >= 3 ? 2048 : 8192) ? 2 : 1;
+    plan.wpa_tan = P.S <= 2 && n_atoms <= 1024 ? 4 : P.S == 1 || n_atoms <= (P.S == 2 ? 16384 : 2048) ? 2 : 1;
     plan.wpa_adj = n_atoms <= (P.n_theta == 16 ? 1536 : bins == 64 ? 8192 : 4096) ? 4 : 2;
   }
   const bool short_rows = n_atoms > 0 && capacity <= 24 * n_atoms;
   if (short_rows && packed_supported(P)) {
     plan.wpa_fwd = plan.wpa_adj = 0;
+    plan.wpa_tan = 1;
   } else if (short_rows && P.S > 1) {
-    // several species: one wave per atom, so that the forward and tangent
-    // passes take one MFMA block per species pair
-    plan.wpa_fwd = 1;
+    // several species: one wave per atom, so that the MFMA passes (the BP
+    // term's forward, the tangent) take one MFMA block per species pair
+    plan.wpa_fwd = plan.wpa_tan = 1;
   }
+  if (bp) plan.wpa_tan = plan.wpa_fwd;
   return plan;
 }
 
