@@ -102,7 +102,7 @@ SOURCES = {"k_fwd_tiles": "desc_tiles.hip", "k_adj_tiles": "desc_tiles.hip", "k_
            "k_nb": "neighbors.hip"}
 
 
-ROWS_MIN_ATOMS = 12288  # fewer atoms take the tile kernel in FP32
+TILES_MOST_ATOMS = 8192  # up to this many take the tile kernel in FP32
 
 
 def mlp_rows_plan(plan, mode, w):
@@ -116,7 +116,7 @@ def mlp_rows_plan(plan, mode, w):
     if len(widths) != 4 or tuple(widths[1:3]) not in shapes:
         return None
     if mode == "fp32":
-        return "k_mlp_rows" if w.params.dim % 4 == 0 and w.system.n_atoms >= ROWS_MIN_ATOMS else None
+        return "k_mlp_rows" if w.params.dim % 4 == 0 and w.system.n_atoms > TILES_MOST_ATOMS else None
     return "k_mlp_rows_bf" if w.params.dim % 8 == 0 else None
 
 

@@ -313,12 +313,12 @@ nn_status nn_energy_forces_noalloc(const nn_system* sys, const nn_nlist* nl, con
  * adjoint passes (1, 2, 4, or 0: the packed passes, four atoms of at most
  * 32 list entries per wave, mBP term) and waves per MLP tile (4, 8, or 1:
  * the row-block MLP, 64 or 128 atoms per block with the weights staged in
- * LDS -- in FP32 below 12288 atoms 16 atoms per block -- for widths
+ * LDS -- in FP32 up to 8192 atoms 16 atoms per block -- for widths
  * (64, 32) and (128, 128), in FP32 also (256, 128), and D a multiple of 4 in
  * FP32, of 8 in the BF16 modes) -- on
  * `stream`, and keeps the fastest for workloads of the same shape class
- * (atom count within a factor of two, 12288 parting two classes, list entries
- * per atom, descriptor sizes, MLP widths and MLP mode) in a process-wide table that
+ * (atom count within a factor of two, list entries per atom, descriptor
+ * sizes, MLP widths and MLP mode) in a process-wide table that
  * nn_energy_forces and nn_energy_forces_grad then use; without an entry
  * they use fixed rules.  Needs a valid list (nn_build_neighbors) and the
  * nn_energy_forces workspace; overwrites the workspace's descriptors and
@@ -337,7 +337,7 @@ nn_status nn_energy_forces_noalloc(const nn_system* sys, const nn_nlist* nl, con
  *     nn_autotune.  One JSON object per line of an array,
  *       {"key": [n_log2, row4, S, n_theta, n_rs_ang, n_rad, h1, h2, mode],
  *        "plan": [f, a, m]}
- *     with n_log2 the bit length of the atom count (15 from 12288 on), row4 =
+ *     with n_log2 the bit length of the atom count (of 8192 that of 8191), row4 =
  *     (ceil(capacity / atoms) + 2) / 4, h1, h2 the first two hidden widths of
  *     species 0 and mode 0 / 1 / 2 for FP32 / BF16 / split BF16.  Plans are
  *     tuned on one GPU model: keep one file per machine type.  A first entry

@@ -140,10 +140,9 @@ static void cache_store_locked() {
 
 static PlanKey plan_key(int64_t n_atoms, int64_t capacity, const DescConst& P, const nn_model* model, int mode) {
   PlanKey k{};
+  // the last count for which the row blocks do not pay joins the class below
   int b = 0;
-  for (int64_t v = n_atoms; v > 0; v >>= 1) ++b;
-  // the class in which the row blocks begin to pay ends there
-  if (mlp_rows_pays(n_atoms) && !mlp_rows_pays((int64_t)1 << (b - 1))) ++b;
+  for (int64_t v = mlp_rows_pays(n_atoms + 1) && !mlp_rows_pays(n_atoms) ? n_atoms - 1 : n_atoms; v > 0; v >>= 1) ++b;
   k.n_log2 = b;
   k.row4 = n_atoms > 0 ? (int)(((capacity + n_atoms - 1) / n_atoms + 2) / 4) : 0;
   k.S = P.S;

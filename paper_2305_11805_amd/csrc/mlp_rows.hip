@@ -759,17 +759,20 @@ bool mlp_rows_supported(int h1, int h2, int D) {
   return ((h1 == 64 && h2 == 32) || (h1 == 128 && h2 == 128) || (h1 == 256 && h2 == 128)) && D % 4 == 0;
 }
 
-// Below this many atoms plan value 1 means the tile kernel, whose block takes 16
+// Up to this many atoms plan value 1 means the tile kernel, whose block takes 16
 // of them, its waves sharing the columns of each product: the larger blocks
 // would leave most CUs without one, and a block's time is then its own chain
-// of chunks.  MLP time in us, row blocks against the tile kernel:
-//   64-32, D 384, 4 species    4227 atoms  33 / 28    8516  35 / 37   17310  40 / 54
-//   64-32, D 152, 1 species    8192 atoms  20 / 17   12288  21 / 20   16384  21 / 28
-//   128-128, D 96, 1 species   8192 atoms  35 / 25   12288  37 / 39   16384  36 / 44
-//   128-128, D 768, 4 species  8192 atoms 104 / 73   12288 103 / 108  16384 104 / 135
-//   256-128, D 152, 1 species  8192 atoms  55 / 52   12288  64 / 75   16384  68 / 97
-constexpr int64_t kRowsMin = 12288;
-bool mlp_rows_pays(int64_t N) { return N >= kRowsMin; }
+// of chunks.  8192 atoms are two tiles for each CU; the next one starts a third
+// round, and the row blocks are ahead from there.  MLP time in us, row blocks
+// against the tile kernel:
+//   64-32, D 384, 4 species    6534 atoms  33 / 29    8571  34 / 36   12213  33 / 36
+//   64-32, D 768, 4 species                           9000  57 / 58   11000  57 / 59
+//   64-32, D 152, 1 species    8000 atoms  18 / 17   10240  19 / 19   16384  21 / 28
+//   128-128, D 96, 1 species   8192 atoms  35 / 25    9000  35 / 35   12000  35 / 37
+//   128-128, D 768, 4 species  8192 atoms 102 / 73    9000 102 / 104  12000 102 / 108
+//   256-128, D 152, 1 species  8000 atoms  57 / 52   10240  60 / 74   16384  66 / 97
+constexpr int64_t kTilesMost = 8192;
+bool mlp_rows_pays(int64_t N) { return N > kTilesMost; }
 
 template <int A, int B, int W>
 static void launch_rows(const MlpArgs& a, int64_t N, hipStream_t s) {

@@ -1,5 +1,5 @@
-"""The shape classes of tuned plans on the host: the FP32 MLP's kernel changes at
-12288 atoms, so a plan tuned on one side of it is not used on the other.  And the
+"""The shape classes of tuned plans on the host: the FP32 MLP's kernel changes past
+8192 atoms, so a plan tuned on one side of it is not used on the other.  And the
 kernels that a plan file names."""
 import json
 import os
@@ -10,7 +10,7 @@ import pytest
 from test_autotune_cache import KEY, QUERY, ROOT, built, write  # noqa: F401
 import test_autotune_cache
 
-CLASSES = [(8191, 13), (8192, 14), (12287, 14), (12288, 15), (16383, 15), (16384, 15), (32767, 15), (32768, 16)]
+CLASSES = [(4095, 12), (4096, 13), (8191, 13), (8192, 13), (8193, 14), (16383, 14), (16384, 15), (32768, 16)]
 
 
 @pytest.mark.parametrize("n,n_log2", CLASSES)
