@@ -1980,8 +1980,9 @@ bool packed_supported(const DescConst& P) {
 // atoms).  16x8 bins: two, each with half the angle terms, since one wave's 128
 // bins leave three waves per SIMD (one species, 64 to 1024 cells of 16 atoms, two
 // waves against one: 28 and 38 us at 1024 atoms, 38 and 41 at 2048, 55 and 65 at
-// 3200, 63 and 70 at 4096, 88 and 95 at 6400, 129 and 132 at 10240; above 16384
-// atoms one, 371 against 376 at 32768); four waves, sharing the triplets, up to
+// 3200, 63 and 70 at 4096, 88 and 95 at 6400, 129 and 132 at 10240; from 16384
+// atoms one, level there in repeated evaluations and 2 us ahead in dynamics, 371
+// against 376 at 32768); four waves, sharing the triplets, up to
 // 768 atoms of at most two species (22 against 29 us).
 // Adjoint: two, which share an atom's records in LDS and so keep more waves
 // resident than one (8x8, one species: 343 against 392 us at 32768 atoms); four
@@ -2005,7 +2006,7 @@ LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity) {
   LaunchPlan plan{w, w, 1};  // the row-block MLP where it takes the shape (FP32), else the tile kernel's default
   if (!bp) {
     const int bins = P.n_theta * P.n_rs_ang;
-    if (bins == 128) plan.wpa_fwd = n_atoms <= 768 && P.S <= 2 ? 4 : n_atoms <= 16384 ? 2 : 1;
+    if (bins == 128) plan.wpa_fwd = n_atoms <= 768 && P.S <= 2 ? 4 : n_atoms <= 12288 ? 2 : 1;
     else plan.wpa_fwd = n_atoms <= 1024 ? 4 : n_atoms <= (P.S >= 3 ? 2048 : 8192) ? 2 : 1;
     plan.wpa_tan = P.S <= 2 && n_atoms <= 1024 ? 4 : P.S == 1 || n_atoms <= (P.S == 2 ? 16384 : 2048) ? 2 : 1;
     plan.wpa_adj = n_atoms <= (P.n_theta == 16 ? 1536 : bins == 64 ? 8192 : 4096) ? 4 : 2;

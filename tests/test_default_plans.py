@@ -39,7 +39,7 @@ def default_plan(S, nt, nq, n, per_atom=60):
 # 16x8 bins hold few waves per SIMD: from 2048 atoms on two waves an atom, in
 # both passes, fill the chip
 @pytest.mark.parametrize("n,waves", [(16, (4, 4)), (768, (4, 4)), (1024, (2, 4)), (1536, (2, 4)), (2048, (2, 2)),
-                                     (4096, (2, 2)), (10240, (2, 2)), (16384, (2, 2)), (16385, (1, 2))])
+                                     (4096, (2, 2)), (12288, (2, 2)), (12289, (1, 2)), (16384, (1, 2))])
 def test_sixteen_angle_terms(n, waves):
     assert default_plan(1, 16, 8, n) == (*waves, 1)
 
