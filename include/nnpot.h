@@ -259,7 +259,8 @@ nn_status nn_build_neighbors(const nn_system* sys, double rc, double skin, nn_nl
 /*
  * Descriptors of every atom: G [device] FP32 [N][D] (layout of
  * nn_mbp_params).  Neighbor entries at r >= rc (skin lists) contribute
- * nothing.  If jac != NULL, also the stored Jacobian jac [device] FP32
+ * nothing, and angular terms of the mBP kind whose Gaussian of the average
+ * radius is below 2^-50 may be left out.  If jac != NULL, also the stored Jacobian jac [device] FP32
  * [capacity][nn_jacobian_stride] (rows as documented there): the
  * derivatives the paper's precomputed-descriptor mode stores (Sec. II.A).
  */

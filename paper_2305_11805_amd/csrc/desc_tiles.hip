@@ -7,7 +7,8 @@
 // A Gaussian R_q = 2^(-d^2), d = sqrt(eta log2 e) (rbar - Rs'_q), is below
 // 2^-50 beyond |d| = kScreen: such a term is under 2^-25 of FP32's
 // resolution of one term of ordinary size, and no sum over an atom's
-// triplets (at most 18336) can see it.  A wave therefore takes its triplets
+// triplets (at most 18336) can see it.  (A bin that holds no larger term is zero
+// here, and below 4e-11 in the passes that form every term.)  A wave therefore takes its triplets
 // in strips of neighbors of like distance, so that the rbar of the 64
 // triplets it holds at a time lie close together, and leaves out a radius
 // term only when all 64 are beyond kScreen of it (one ballot per term, exact
@@ -1175,7 +1176,8 @@ __device__ __forceinline__ void adj_tiles_atom(int64_t i, const nn_system& sys, 
 
 // Two or more waves an atom share its records, and the LDS then holds six
 // waves per SIMD: 80 registers each (the same loop takes 97 unasked, 5 waves
-// per SIMD: 812 against 774 us for 65536 atoms of 52 neighbors).
+// per SIMD: 812 against 774 us for 65536 atoms of 52 neighbors).  8x4 bins of one
+// species then keep 20 bytes a lane in scratch.
 template <int NT, int NRA, bool ONE_SPECIES, int WPA, int ZC>
 __global__ void __launch_bounds__(64 * WPA, WPA > 1 && NT <= 8 ? (ZC > 0 ? 6 : 5) : 4) k_adj_tiles(nn_system sys, const int64_t* __restrict__ offsets,
                                                         const int32_t* __restrict__ nbr,
