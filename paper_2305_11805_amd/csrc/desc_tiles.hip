@@ -736,8 +736,8 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
 
 // Waves per SIMD that the registers of a wave's bins leave.  At these bounds the
 // 8x8 passes keep up to 64 bytes a lane in scratch with three or more species, 20
-// with fewer and several waves, and 128 bins 12 to 84: bins and terms of the
-// inner loop stay in registers.
+// with fewer and several waves, and 128 bins 12 to 84: with three or more species
+// six to nine accesses for each 64 triplets of a wave's loop, else none to two.
 constexpr int fwd_waves(int NT, int NRA, int WPA, bool MANY) {
   const bool half = NT * NRA == 128 && WPA == 2;  // AS = 2
   const int bins = NT * NRA / (half ? 2 : 1);
