@@ -462,18 +462,18 @@ struct StripTri {
 };
 
 // The descriptor row of atom i by the block (WPA waves).  MANY: three or
-// more species.  The waves share the triplets; two waves of 16x8 bins share the
-// angle terms instead (AS = 2): each takes all triplets with eight terms, in 96
+// more species.  The waves share the triplets (AS = 1), or two waves of 16x8 bins
+// the angle terms (AS = 2): each then takes all triplets with eight terms, in 96
 // registers and five waves per SIMD where 128 bins take 168 and three, and no
 // sums pass between them.  4096 atoms of 52 neighbors 69 -> 63 us, 2048 44 -> 38,
-// for the triplets' geometry formed twice (one wave at 65536 atoms: 717, two 732).
-template <int NT, int NRA, int WPA, int ZC, bool MANY>
+// for the triplets' geometry formed twice: where three waves per SIMD hold all
+// atoms (up to 1536) the shared triplets take 30 against 36 us.
+template <int NT, int NRA, int WPA, int ZC, bool MANY, int AS = 1>
 __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn_system& sys,
                                                const int64_t* __restrict__ offsets, const int32_t* __restrict__ nbr,
                                                const int8_t* __restrict__ shift, const DescConst& P,
                                                float* __restrict__ G, int64_t* meta) {
   constexpr int NB = NT * NRA;
-  constexpr int AS = NT * NRA == 128 && WPA == 2 ? 2 : 1;
   constexpr int TW = WPA / AS;              // waves that share the triplets
   constexpr int NTW = NT / AS;              // angle terms of a wave
   constexpr int NBW = NTW * NRA;            // and its bins of a species-pair block
@@ -738,13 +738,12 @@ __device__ __forceinline__ void fwd_tiles_atom(int64_t i, bool list_ok, const nn
 // 8x8 passes keep up to 64 bytes a lane in scratch with three or more species, 20
 // with fewer and several waves, and 128 bins 12 to 84: with three or more species
 // six to nine accesses for each 64 triplets of a wave's loop, else none to two.
-constexpr int fwd_waves(int NT, int NRA, int WPA, bool MANY) {
-  const bool half = NT * NRA == 128 && WPA == 2;  // AS = 2
-  const int bins = NT * NRA / (half ? 2 : 1);
-  return bins <= 32 ? 6 : bins > 64 ? 3 : NT == 8 || (half && !MANY) ? 5 : 4;
+constexpr int fwd_waves(int NT, int NRA, int AS, bool MANY) {
+  const int bins = NT * NRA / AS;
+  return bins <= 32 ? 6 : bins > 64 ? 3 : NT == 8 || (AS == 2 && !MANY) ? 5 : 4;
 }
 
-template <int NT, int NRA, int WPA, int ZC, bool MANY, int WAVES = fwd_waves(NT, NRA, WPA, MANY)>
+template <int NT, int NRA, int WPA, int ZC, bool MANY, int AS = 1, int WAVES = fwd_waves(NT, NRA, AS, MANY)>
 __global__ void __launch_bounds__(64 * WPA, WAVES) k_fwd_tiles(nn_system sys, const int64_t* __restrict__ offsets,
                                                         const int32_t* __restrict__ nbr,
                                                         const int8_t* __restrict__ shift, DescConst P,
@@ -754,7 +753,7 @@ __global__ void __launch_bounds__(64 * WPA, WAVES) k_fwd_tiles(nn_system sys, co
   const int64_t i = atom_of_block(order, sys.n_atoms, list_ok);
   if (i < 0) return;
   if (one.perm && threadIdx.x == 0) identity_group(one, sys, i, meta);
-  fwd_tiles_atom<NT, NRA, WPA, ZC, MANY>(i, list_ok, sys, offsets, nbr, shift, P, G, meta);
+  fwd_tiles_atom<NT, NRA, WPA, ZC, MANY, AS>(i, list_ok, sys, offsets, nbr, shift, P, G, meta);
 }
 
 // The atoms a packed launch leaves out (rows over kPackNb entries), one
@@ -1215,22 +1214,30 @@ __global__ void __launch_bounds__(64) k_adj_tiles_long(nn_system sys, const int6
 // launchers
 // ---------------------------------------------------------------------------
 
-template <int NT, int NRA, int WPA, int ZC, bool MANY>
+template <int NT, int NRA, int WPA, int ZC, bool MANY, int... SHARE>
 static void fwd_w(const nn_system& sys, const nn_nlist& nl, const DescConst& P, float* G, IdentityGroup one,
                   hipStream_t s) {
-  // Up to 2048 atoms two waves each are at most four for each of the 1024 SIMDs.
-  // Where a fifth fits, some get five and others three (after a list build 42 us at
-  // 2048 atoms); where only four do, each gets its share (38 us).  More atoms need
-  // the fifth: 42 against 47 us at 2064.
-  if constexpr (fwd_waves(NT, NRA, WPA, MANY) == 5 && NT == 16) {
-    if (sys.n_atoms <= 2048) {
-      hipLaunchKernelGGL((k_fwd_tiles<NT, NRA, WPA, ZC, MANY, 4>), dim3(atom_grid(sys.n_atoms, nl.order)),
-                         dim3(64 * WPA), 0, s, sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
-      return;
-    }
+  hipLaunchKernelGGL((k_fwd_tiles<NT, NRA, WPA, ZC, MANY, SHARE...>), dim3(atom_grid(sys.n_atoms, nl.order)),
+                     dim3(64 * WPA), 0, s, sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
+}
+
+// Two waves an atom.  16x8 bins: the triplets shared while three waves for each of
+// the 1024 SIMDs hold them all (three or more species: 42 us with the terms shared,
+// 50 with four waves at 600 atoms, and never less), else the terms.  Up to 2048
+// atoms four waves per SIMD do: where a fifth fits, some SIMDs get five and others
+// three (after a list build 42 us at 2048 atoms); where only four do, each gets its
+// share (38 us).  More atoms need the fifth: 42 against 47 us at 2064.
+template <int NT, int NRA, int ZC, bool MANY>
+static void fwd_two(const nn_system& sys, const nn_nlist& nl, const DescConst& P, float* G, IdentityGroup one,
+                    hipStream_t s) {
+  if constexpr (NT * NRA == 128) {
+    if (MANY) fwd_w<NT, NRA, 2, ZC, MANY, 2>(sys, nl, P, G, one, s);
+    else if (sys.n_atoms <= 1536) fwd_w<NT, NRA, 2, ZC, MANY, 1>(sys, nl, P, G, one, s);
+    else if (sys.n_atoms <= 2048) fwd_w<NT, NRA, 2, ZC, MANY, 2, 4>(sys, nl, P, G, one, s);
+    else fwd_w<NT, NRA, 2, ZC, MANY, 2>(sys, nl, P, G, one, s);
+  } else {
+    fwd_w<NT, NRA, 2, ZC, MANY>(sys, nl, P, G, one, s);
   }
-  hipLaunchKernelGGL((k_fwd_tiles<NT, NRA, WPA, ZC, MANY>), dim3(atom_grid(sys.n_atoms, nl.order)), dim3(64 * WPA), 0, s,
-                     sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
 }
 
 template <int NT, int NRA, int ZC, bool MANY>
@@ -1240,7 +1247,7 @@ static void fwd_z(const nn_system& sys, const nn_nlist& nl, const DescConst& P, 
     hipLaunchKernelGGL((k_fwd_tiles_long<NT, NRA, ZC, MANY>), dim3((unsigned)((sys.n_atoms + kWave - 1) / kWave)), dim3(64),
                        0, s, sys, nl.offsets, nl.nbr, nl.shift, P, G, nl.meta, one, nl.order);
   else if (wpa == 4) fwd_w<NT, NRA, 4, ZC, MANY>(sys, nl, P, G, one, s);
-  else if (wpa == 2) fwd_w<NT, NRA, 2, ZC, MANY>(sys, nl, P, G, one, s);
+  else if (wpa == 2) fwd_two<NT, NRA, ZC, MANY>(sys, nl, P, G, one, s);
   else fwd_w<NT, NRA, 1, ZC, MANY>(sys, nl, P, G, one, s);
 }
 

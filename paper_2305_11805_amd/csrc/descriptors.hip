@@ -1977,21 +1977,24 @@ bool packed_supported(const DescConst& P) {
 // four waves 20 us, two 22, one 33 at 1024 atoms; 48, 45 and 48 at 4096; 90, 79
 // and 79 at 8192); three or more species have short species-pair blocks that
 // more waves cannot share (four species: one wave 68, two 82 us at 4096
-// atoms).  16x8 bins: two, each with half the angle terms, since one wave's 128
-// bins leave three waves per SIMD (one species, 64 to 1024 cells of 16 atoms, two
-// waves against one: 28 and 38 us at 1024 atoms, 38 and 41 at 2048, 55 and 65 at
-// 3200, 63 and 70 at 4096, 88 and 95 at 6400, 129 and 132 at 10240; from 16384
+// atoms).  16x8 bins: two, from 1537 atoms with half the angle terms each, since one
+// wave's 128 bins leave three waves per SIMD (one species, cells of 16 atoms, two
+// waves against one: 26 and 38 us at 1024 atoms, 30 and 39 at 1536, 38 and 41 at
+// 2048, 55 and 65 at 3200, 63 and 70 at 4096, 129 and 132 at 10240; from 16384
 // atoms one, level there in repeated evaluations and 2 us ahead in dynamics, 371
 // against 376 at 32768); four waves, sharing the triplets, up to
-// 768 atoms of at most two species (22 against 29 us).
+// 768 atoms of at most two species (22 against 26 us).
 // Adjoint: two, which share an atom's records in LDS and so keep more waves
 // resident than one (8x8, one species: 343 against 392 us at 32768 atoms); four
 // for few atoms.  That line lies where four waves an atom fill the chip: later
 // the more registers a wave needs, earlier the less there is to share.  Four
 // against two, us: 8x8 58 and 61 at 4096 atoms, 107 and 107 at 8192 (two species
 // 190 and 204); 8x4 45 and 46 at 4096, 84 and 79 at 8192 (4x8 81 and 77, 4x4 72
-// and 66); 16x8, which holds four waves per SIMD, 40 and 44 at 1536, 47 and 44 at
-// 2048, 81 and 78 at 4096, 150 and 138 at 8192 (16x4 the same way).
+// and 66).  16x8 holds four waves per SIMD, so that two waves an atom fill one round
+// at 2048 atoms, four at 1024: four against two 40 and 44 at 1536, 44 and 45 at
+// 1792, 47 and 44 at 2048, 51 and 56 at 2240, 56 and 59 at 2560, 68 and 68 at 3200,
+// 81 and 78 at 4096, 150 and 138 at 8192 (16x4 32 and 36 at 1500, 38 and 36 at 2048,
+// 53 and 51 at 3000).
 // Tangent (MFMA, triplets in index order; mBP), us with four, two and one wave:
 // one species 17, 25 and 39 at 16 atoms, 26, 32 and 47 at 1024, 69, 71 and 90 at
 // 4096, 250, 246 and 272 at 16384, 965, 927 and 985 at 65536; two species the same
@@ -2009,7 +2012,8 @@ LaunchPlan plan_default(int64_t n_atoms, const DescConst& P, int64_t capacity) {
     if (bins == 128) plan.wpa_fwd = n_atoms <= 768 && P.S <= 2 ? 4 : n_atoms <= 12288 ? 2 : 1;
     else plan.wpa_fwd = n_atoms <= 1024 ? 4 : n_atoms <= (P.S >= 3 ? 2048 : 8192) ? 2 : 1;
     plan.wpa_tan = P.S <= 2 && n_atoms <= 1024 ? 4 : P.S == 1 || n_atoms <= (P.S == 2 ? 16384 : 2048) ? 2 : 1;
-    plan.wpa_adj = n_atoms <= (P.n_theta == 16 ? 1536 : bins == 64 ? 8192 : 4096) ? 4 : 2;
+    if (P.n_theta == 16) plan.wpa_adj = n_atoms <= 1856 || (n_atoms > 2048 && n_atoms <= 2560) ? 4 : 2;
+    else plan.wpa_adj = n_atoms <= (bins == 64 ? 8192 : 4096) ? 4 : 2;
   }
   const bool short_rows = n_atoms > 0 && capacity <= 24 * n_atoms;
   if (short_rows && packed_supported(P)) {
