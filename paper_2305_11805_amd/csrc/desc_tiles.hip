@@ -1222,9 +1222,10 @@ static void fwd_w(const nn_system& sys, const nn_nlist& nl, const DescConst& P, 
 }
 
 // Two waves an atom.  16x8 bins: the triplets shared while three waves for each of
-// the 1024 SIMDs hold them all (three or more species: 42 us with the terms shared,
-// 50 with four waves at 600 atoms, and never less), else the terms.  Up to 2048
-// atoms four waves per SIMD do: where a fifth fits, some SIMDs get five and others
+// the 1024 SIMDs hold them all, else the terms; three or more species share the
+// terms at every count, since their pair blocks have few triplets to share (four
+// species 44 us at 1024 atoms, with one wave 67, before 54).  Up to 2048 atoms four
+// waves per SIMD do: where a fifth fits, some SIMDs get five and others
 // three (after a list build 42 us at 2048 atoms); where only four do, each gets its
 // share (38 us).  More atoms need the fifth: 42 against 47 us at 2064.
 template <int NT, int NRA, int ZC, bool MANY>
